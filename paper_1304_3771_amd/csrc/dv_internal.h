@@ -22,6 +22,11 @@ struct DSlot {
     uint64_t arena_off;
 };
 
+// Every VM's sorted memslots lie in one table, kSlotRow records a VM (the most
+// it can have), unused ones with gpa ~0: a kernel that knows the VM's number
+// loads them without waiting for the VM's own record.
+constexpr uint32_t kSlotRow = 64;
+
 // Per-VM device view.  `index` holds one word per 2 MiB of guest-physical
 // space below index_len * 2 MiB:
 //   0                 no slot overlaps the block
@@ -54,6 +59,7 @@ struct DProc {
 struct DView {
     const DVm *vms;
     const DProc *procs;
+    const DSlot *slots;  // kSlotRow per VM
     uint32_t nvm;
     uint32_t nproc;
     uint32_t lds;      // kernels: the VMs' memslots are in the workgroup's LDS (set by the kernel)
@@ -178,6 +184,28 @@ struct DBatch {
     uint32_t pad1;
 };
 
+// One per-request copy (k_plain_walk).  What the process id names is fixed
+// when the process is created, so it is passed by value; the VM's record, its
+// memslots and its EPT root are read from the device tables.
+struct PlainArgs {
+    DView v;
+    uint64_t cr3;
+    uint64_t gva;
+    uint64_t host;
+    devirt_result *res;
+    DSeg *segs;         // one per copied page (not inline: k_copy moves them)
+    DEpochCtr *ctr;     // their count
+    uint32_t vm;
+    uint32_t levels;
+    uint32_t len;
+    uint32_t dir;
+    uint32_t code0;     // known before the walk: unknown process, range not user-canonical
+    uint32_t inline_copy;
+    uint32_t nontemporal;
+    uint32_t pad;
+};
+constexpr uint32_t kPlainWaves = 16;  // wavefronts of the one workgroup, at most
+
 // ---- launchers (kernels.hip) ------------------------------------------------
 hipError_t launch_reset(hipStream_t s, DBatch b, uint32_t n_epochs);
 hipError_t launch_translate_groups(hipStream_t s, int grid, int block, DView v, DBatch b, uint64_t r0,
@@ -187,6 +215,7 @@ hipError_t launch_translate_large(hipStream_t s, int grid, int block, DView v, D
 hipError_t launch_copy(hipStream_t s, int grid, int block, DBatch b, uint32_t epoch);
 hipError_t launch_spill(hipStream_t s, int grid, int block, DView v, DBatch b, uint64_t r0, uint64_t r1,
                         uint32_t epoch);
+hipError_t launch_plain_walk(hipStream_t s, uint32_t waves, const PlainArgs &a);
 hipError_t launch_plain(hipStream_t s, DView v, DBatch b, devirt_request req, int inline_copy);
 hipError_t launch_xlat(hipStream_t s, int grid, int block, DView v, uint32_t asid, const uint64_t *gva,
                        uint64_t n, uint32_t flags, devirt_xlat *out, DCounters *counters);

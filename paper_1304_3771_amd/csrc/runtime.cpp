@@ -143,9 +143,9 @@ extern "C" int devirt_close(devirt_ctx *c) {
     for (auto &vm : c->vms) {
         hipFree(vm.arena);
         hipFree(vm.d_index);
-        hipFree(vm.d_slots);
     }
     hipFree(c->d_vms);
+    hipFree(c->d_slots);
     hipFree(c->d_procs);
     hipFree(c->d_fifo);
     hipFree(c->d_counters);
@@ -158,29 +158,57 @@ extern "C" int devirt_close(devirt_ctx *c) {
     return 0;
 }
 
-// Re-upload the VM table (after a VM or memslot change).  Device must be idle.
-static int upload_vms(devirt_ctx *c) {
+// A VM's memslots as the device table holds them: sorted, unused records with gpa ~0.
+static void slot_row(const VmHost &v, DSlot *row) {
+    uint32_t n = 0;
+    for (const auto &s : v.slots)
+        if (s.used) row[n++] = DSlot{s.gpa, s.gpa + s.bytes, s.off};
+    std::sort(row, row + n, [](const DSlot &a, const DSlot &b) { return a.gpa < b.gpa; });
+    for (; n < kSlotRow; ++n) row[n] = DSlot{~0ull, 0, 0};
+}
+
+// Re-upload the VM table (after a VM or memslot change) and VM `changed`'s row
+// of the memslot table.  Device must be idle.
+static int upload_vms(devirt_ctx *c, size_t changed) {
+    if (c->vms.size() > c->d_vms_cap) {
+        const size_t cap = std::max<size_t>(16, c->vms.size() * 2);
+        DVm *p = nullptr;
+        HIPCHK(hipMalloc(&p, cap * sizeof(DVm)));
+        DSlot *q = nullptr;
+        if (hipMalloc(&q, cap * kSlotRow * sizeof(DSlot)) != hipSuccess) {
+            hipFree(p);
+            return dv_fail(-ENOMEM, "hipMalloc memslot table");
+        }
+        if (c->d_slots && hipMemcpy(q, c->d_slots, c->d_vms_cap * kSlotRow * sizeof(DSlot), hipMemcpyDeviceToDevice) !=
+                              hipSuccess) {
+            hipFree(p);
+            hipFree(q);
+            return dv_fail(-EIO, "cannot copy the memslot table");
+        }
+        hipFree(c->d_vms);
+        hipFree(c->d_slots);
+        c->d_vms = p;
+        c->d_slots = q;
+        c->d_vms_cap = cap;
+    }
+    if (changed < c->vms.size()) {
+        DSlot row[kSlotRow];
+        slot_row(c->vms[changed], row);
+        HIPCHK(hipMemcpy(c->d_slots + changed * kSlotRow, row, sizeof row, hipMemcpyHostToDevice));
+    }
     std::vector<DVm> h(c->vms.size());
     for (size_t i = 0; i < c->vms.size(); ++i) {
         const VmHost &v = c->vms[i];
         h[i].arena = v.arena;
         h[i].arena_bytes = v.bytes;
         h[i].index = v.d_index;
-        h[i].slots = v.d_slots;
+        h[i].slots = c->d_slots + i * kSlotRow;
         h[i].index_len = v.index_len;
         h[i].nslots = v.nsorted;
         h[i].index_complete = v.index_complete;
         h[i].lds_base = kLdsNone;
         h[i].lds_idx = kLdsNone;
         h[i].ept_root = v.ept_root;
-    }
-    if (c->vms.size() > c->d_vms_cap) {
-        size_t cap = std::max<size_t>(16, c->vms.size() * 2);
-        DVm *p = nullptr;
-        HIPCHK(hipMalloc(&p, cap * sizeof(DVm)));
-        hipFree(c->d_vms);
-        c->d_vms = p;
-        c->d_vms_cap = cap;
     }
     if (!h.empty()) HIPCHK(hipMemcpy(c->d_vms, h.data(), h.size() * sizeof(DVm), hipMemcpyHostToDevice));
     c->tables_version++;
@@ -229,7 +257,7 @@ extern "C" int devirt_vm_create(devirt_ctx *c, uint64_t arena_bytes, uint32_t *v
     }
     v.bytes = arena_bytes;
     c->vms.push_back(v);
-    int rc = upload_vms(c);
+    int rc = upload_vms(c, c->vms.size() - 1);
     if (rc) return rc;
     *vm = (uint32_t)(c->vms.size() - 1);
     return 0;
@@ -327,28 +355,18 @@ extern "C" int devirt_memslot_set(devirt_ctx *c, uint32_t vm, uint32_t slot, uin
     std::vector<uint64_t> index;
     uint32_t complete = 1;
     build_slot_index(nv, sorted, index, complete);
-    DSlot *ds = nullptr;
     uint64_t *di = nullptr;
-    if (!sorted.empty()) {
-        if (hipMalloc(&ds, sorted.size() * sizeof(DSlot)) != hipSuccess) return dv_fail(-ENOMEM, "hipMalloc slots");
-        HIPCHK(hipMemcpy(ds, sorted.data(), sorted.size() * sizeof(DSlot), hipMemcpyHostToDevice));
-    }
     if (!index.empty()) {
-        if (hipMalloc(&di, index.size() * 8) != hipSuccess) {
-            hipFree(ds);
-            return dv_fail(-ENOMEM, "hipMalloc slot index");
-        }
+        if (hipMalloc(&di, index.size() * 8) != hipSuccess) return dv_fail(-ENOMEM, "hipMalloc slot index");
         HIPCHK(hipMemcpy(di, index.data(), index.size() * 8, hipMemcpyHostToDevice));
     }
-    hipFree(v.d_slots);
     hipFree(v.d_index);
     v = nv;
-    v.d_slots = ds;
     v.d_index = di;
     v.nsorted = (uint32_t)sorted.size();
     v.index_len = (uint32_t)index.size();
     v.index_complete = complete;
-    return upload_vms(c);
+    return upload_vms(c, vm);
 }
 
 extern "C" int devirt_vm_set_ept(devirt_ctx *c, uint32_t vm, uint64_t root) {
@@ -361,7 +379,7 @@ extern "C" int devirt_vm_set_ept(devirt_ctx *c, uint32_t vm, uint64_t root) {
     if (set_dev(c)) return -EIO;
     HIPCHK(hipDeviceSynchronize());
     v.ept_root = root;
-    return upload_vms(c);
+    return upload_vms(c, vm);
 }
 
 extern "C" int devirt_process_create(devirt_ctx *c, uint32_t vm, uint64_t cr3_gpa, uint32_t levels, uint32_t *asid) {
@@ -386,6 +404,7 @@ DView view_of(const devirt_ctx *c) {
     DView v;
     v.vms = c->d_vms;
     v.procs = c->d_procs;
+    v.slots = c->d_slots;
     v.nvm = (uint32_t)c->vms.size();
     v.nproc = (uint32_t)c->procs.size();
     v.lds = 0;
@@ -765,7 +784,17 @@ static uint64_t pages_of(uint64_t gva, uint64_t len) {
     return ((gva + len - 1) >> 12) - (gva >> 12) + 1;
 }
 
-static const uint64_t kPlainInlinePages = 16;
+// A request of at most this many pages is walked and copied by one workgroup
+// in one launch; a longer one's pages go to the copy kernel.  Back-to-back
+// calls, one launch against two: 64 KiB 6.4 against 8.2 us, 128 KiB 7.4
+// against 8.1, 200 KB (49 pages) 8.4 against 8.3, 512 KiB 9.4 against 8.6.
+static const uint64_t kPlainInlinePages = 40;
+
+// The range check of a request of a process with `levels`-deep tables.
+static uint32_t range_code(uint64_t gva, uint64_t len, uint32_t levels) {
+    const uint64_t lim = levels == 5 ? 1ull << 56 : levels == 3 ? 1ull << 32 : 1ull << 47;
+    return len != 0 && (gva >= lim || len > lim - gva) ? DEVIRT_NONCANONICAL : DEVIRT_OK;
+}
 
 int plain_copy(devirt_ctx *c, uint32_t asid, uint64_t gva, uint64_t host, uint64_t len, uint32_t dir,
                devirt_result *res, void *stream, const StaticScratch *st) {
@@ -777,14 +806,16 @@ int plain_copy(devirt_ctx *c, uint32_t asid, uint64_t gva, uint64_t host, uint64
     if (set_dev(c)) return -EIO;
     hipStream_t s = (hipStream_t)stream;
     const uint64_t pages = pages_of(gva, len);
+    if (st && pages > st->cap)  // the caller's static scratch: nothing is allocated
+        return dv_fail(-EINVAL, "the request touches %llu pages; this entry point takes at most %llu",
+                       (unsigned long long)pages, (unsigned long long)st->cap);
+    // The translation cache and the device counters belong to the walk by one
+    // wavefront (k_plain); every other request is walked by k_plain_walk.
+    const bool one_wave = c->cfg.fifo_entries != 0 || (c->profiling & DEVIRT_PROF_COUNTERS);
     const bool inl = pages <= kPlainInlinePages;
     int rc;
     DBatch b;
     if (st) {
-        // the caller's static scratch: nothing is allocated
-        if (pages > st->cap)
-            return dv_fail(-EINVAL, "the request touches %llu pages; this entry point takes at most %llu",
-                           (unsigned long long)pages, (unsigned long long)st->cap);
         b = make_batch(c, nullptr);
         b.segs = st->segs;
         b.shorts = st->shorts;
@@ -792,28 +823,58 @@ int plain_copy(devirt_ctx *c, uint32_t asid, uint64_t gva, uint64_t host, uint64
         b.t0 = st->t0;
         b.part_cap = st->cap;
     } else {
-        Workspace *w = get_ws(c, s);
-        if ((rc = ensure_ws(c, w, 1, 1, false, inl ? 0 : pages))) return rc;
+        Workspace *w = nullptr;
+        if (one_wave || !inl) {
+            w = get_ws(c, s);
+            if ((rc = ensure_ws(c, w, 1, 1, false, inl ? 0 : pages))) return rc;
+        }
         b = make_batch(c, w);
         // one request: part 0 spans the whole queue, which holds at least one
         // segment per page, so no run overflows it
-        b.part_cap = std::min(w->seg_cap, w->short_cap);
+        if (w) b.part_cap = std::min(w->seg_cap, w->short_cap);
     }
-    b.res = res;
-    if (c->cfg.fifo_entries) {
-        b.fifo = c->d_fifo;
-        b.fifo_entries = c->cfg.fifo_entries;
-        b.xlat_gen = c->xlat_gen;
-    }
-    devirt_request rq;
-    memset(&rq, 0, sizeof rq);
-    rq.gva = gva;
-    rq.host = host;
-    rq.len = (uint32_t)len;
-    rq.asid = asid;
-    rq.dir = (uint8_t)dir;
     c->stats.plain_calls++;
-    HIPCHK(launch_plain(s, view_of(c), b, rq, inl ? 1 : 0));
+    if (one_wave) {
+        b.res = res;
+        if (c->cfg.fifo_entries) {
+            b.fifo = c->d_fifo;
+            b.fifo_entries = c->cfg.fifo_entries;
+            b.xlat_gen = c->xlat_gen;
+        }
+        devirt_request rq;
+        memset(&rq, 0, sizeof rq);
+        rq.gva = gva;
+        rq.host = host;
+        rq.len = (uint32_t)len;
+        rq.asid = asid;
+        rq.dir = (uint8_t)dir;
+        HIPCHK(launch_plain(s, view_of(c), b, rq, inl ? 1 : 0));
+    } else {
+        PlainArgs a;
+        memset(&a, 0, sizeof a);
+        a.v = view_of(c);
+        a.gva = gva;
+        a.host = host;
+        a.len = (uint32_t)len;
+        a.dir = dir;
+        a.res = res;
+        a.segs = b.segs;
+        a.ctr = b.ctr;
+        a.inline_copy = inl ? 1 : 0;
+        a.nontemporal = b.nontemporal;
+        if (asid >= c->procs.size()) {
+            a.code0 = DEVIRT_INVALID;
+        } else {
+            const DProc &p = c->procs[asid];
+            a.vm = p.vm;
+            a.levels = p.levels;
+            a.cr3 = p.cr3;
+            a.code0 = range_code(gva, len, p.levels);
+        }
+        // inline: a wavefront per page to copy; else one per 64 pages to walk
+        const uint64_t waves = a.code0 ? 1 : inl ? pages : (pages + 63) / 64;
+        HIPCHK(launch_plain_walk(s, (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(waves, kPlainWaves)), a));
+    }
     if (!inl) {
         ProfEv *pe = nullptr;
         if (!st && (rc = prof_begin(c, s, 0, &pe))) return rc;

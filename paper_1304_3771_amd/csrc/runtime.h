@@ -16,7 +16,6 @@ struct VmHost {
         bool used = false;
     } slots[64];
     uint64_t *d_index = nullptr;
-    dv::DSlot *d_slots = nullptr;
     uint32_t index_len = 0, nsorted = 0, index_complete = 1;
     uint64_t ept_root = ~0ull;  // ~0: translate through the memslots
 };
@@ -72,6 +71,7 @@ struct devirt_ctx {
     std::vector<VmHost> vms;
     std::vector<dv::DProc> procs;
     dv::DVm *d_vms = nullptr;
+    dv::DSlot *d_slots = nullptr;  // kSlotRow per VM, sorted, as many rows as d_vms has records
     size_t d_vms_cap = 0;
     dv::DProc *d_procs = nullptr;
     size_t d_procs_cap = 0;
