@@ -34,6 +34,10 @@ constexpr uint32_t kSlotRow = 64;
 //                     (delta = arena_off - slot gpa, 4 KiB aligned, mod 2^64)
 //   1                 the block is split between slots / holes: search slots
 // When index_complete is set, no slot lies at or above index_len * 2 MiB.
+// `words` holds the first nwords blocks of the index as 32-bit words, for a
+// kernel to keep in LDS: a covered block as (delta / 4 KiB) << 2 | 2 (as 1 if
+// that does not fit 30 signed bits), the others as above.
+constexpr uint32_t kIndexWords = 3072;  // 6 GiB of guest-physical space
 struct DVm {
     uint8_t *arena;
     uint64_t arena_bytes;
@@ -44,7 +48,8 @@ struct DVm {
     uint32_t index_complete;
     uint32_t lds_base;  // kernels: this VM's first slot in the workgroup's LDS copy (kLdsNone: use HBM)
     uint64_t ept_root;  // arena offset of the EPT's level-4 table; kNoEpt: memslots translate
-    uint32_t lds_idx;   // kernels: this VM's 2 MiB index in LDS, in 32-bit words (kLdsNone: none)
+    const uint32_t *words;
+    uint32_t nwords;
     uint32_t pad;
 };
 constexpr uint32_t kLdsNone = 0xFFFFFFFFu;
@@ -62,9 +67,7 @@ struct DView {
     const DSlot *slots;  // kSlotRow per VM
     uint32_t nvm;
     uint32_t nproc;
-    uint32_t lds;      // kernels: the VMs' memslots are in the workgroup's LDS (set by the kernel)
-    uint32_t lds_idx;  // kernels: first LDS word of VM lds_idx_vm's 2 MiB index (kLdsNone: none)
-    uint32_t lds_idx_vm;
+    uint32_t lds;  // kernels: the VMs' memslots are in the workgroup's LDS (set by the kernel)
     uint32_t pad;
 };
 
@@ -206,6 +209,20 @@ struct PlainArgs {
 };
 constexpr uint32_t kPlainWaves = 16;  // wavefronts of the one workgroup, at most
 
+// One translate-only call (k_xlat).
+struct XlatArgs {
+    DView v;
+    uint64_t cr3;
+    const uint64_t *gva;
+    uint64_t n;
+    devirt_xlat *out;
+    DCounters *counters;  // null unless profiling
+    uint32_t vm;
+    uint32_t levels;      // 0: unknown process
+    uint32_t flags;
+    uint32_t pad;
+};
+
 // ---- launchers (kernels.hip) ------------------------------------------------
 hipError_t launch_reset(hipStream_t s, DBatch b, uint32_t n_epochs);
 hipError_t launch_translate_groups(hipStream_t s, int grid, int block, DView v, DBatch b, uint64_t r0,
@@ -217,8 +234,7 @@ hipError_t launch_spill(hipStream_t s, int grid, int block, DView v, DBatch b, u
                         uint32_t epoch);
 hipError_t launch_plain_walk(hipStream_t s, uint32_t waves, const PlainArgs &a);
 hipError_t launch_plain(hipStream_t s, DView v, DBatch b, devirt_request req, int inline_copy);
-hipError_t launch_xlat(hipStream_t s, int grid, int block, DView v, uint32_t asid, const uint64_t *gva,
-                       uint64_t n, uint32_t flags, devirt_xlat *out, DCounters *counters);
+hipError_t launch_xlat(hipStream_t s, int grid, int block, const XlatArgs &a);
 hipError_t launch_fault_count(hipStream_t s, const devirt_result *res, uint64_t n, uint32_t *tile_cnt);
 hipError_t launch_fault_scan(hipStream_t s, uint32_t *tile_cnt, uint64_t ntiles, uint64_t *n_faults);
 hipError_t launch_fault_scatter(hipStream_t s, const devirt_result *res, uint64_t n, const uint32_t *tile_off,

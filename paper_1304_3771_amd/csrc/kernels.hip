@@ -117,50 +117,6 @@ constexpr uint32_t kLdsVms = 64;
 __shared__ DSlot g_lds_slot[kLdsSlots];
 __shared__ uint32_t g_lds_off[kLdsVms + 1];
 
-// A VM's 2 MiB index in the LDS area after the slots (from word w0), when it
-// fits: one 32-bit word per block, a block inside one slot as (arena_off -
-// gpa) / 4 KiB << 2 | 2 (that difference must fit 30 signed bits), a block
-// split between slots as 1, a block without a slot as 0.  Entered by every
-// thread; ends with a barrier.  Returns (uniformly) w0, or kLdsNone.
-typedef DV_GLOBAL DVm g_dvm;
-__device__ uint32_t lds_index_load(const g_dvm *vm, uint32_t w0) {
-    const uint32_t nblk = vm->index_len;
-    const bool fits = vm->ept_root == kNoEpt && nblk > 0 && w0 + nblk <= kLdsSlots * (uint32_t)(sizeof(DSlot) / 4);
-    int bad = 0;
-    if (fits) {
-        uint32_t *words = (uint32_t *)g_lds_slot + w0;
-        for (uint32_t b = threadIdx.x; b < nblk; b += blockDim.x) {
-            const uint64_t e = gp<const g_u64>(vm->index)[b];
-            uint32_t x = (uint32_t)(e & 1u);
-            if (e & 2) {
-                const int64_t dp = (int64_t)(e & ~0xFFFull) >> 12;
-                if (dp < -(1ll << 29) || dp >= (1ll << 29)) bad = 1;
-                x = ((uint32_t)(int32_t)dp << 2) | 2u;
-            }
-            words[b] = x;
-        }
-    }
-    bad = __syncthreads_or(bad);
-    return fits && !bad ? w0 : kLdsNone;
-}
-
-// Fills the workgroup's copy with VM `one`'s slots only (at LDS slot 0),
-// followed by its 2 MiB index when that fits (V.lds_idx, V.lds_idx_vm);
-// entered by every thread.  Returns (uniformly) whether the slots are in LDS.
-__device__ bool lds_slots_load_one(DView &V, uint32_t one) {
-    V.lds_idx = kLdsNone;
-    if (one >= V.nvm) return false;
-    typedef DV_GLOBAL DSlot g_slot;
-    const g_dvm *vm = gp<const g_dvm>(V.vms) + one;
-    const uint32_t ns = vm->nslots;
-    if (ns > kLdsSlots || one > kLdsVms) return false;
-    if (threadIdx.x == 0) g_lds_off[one] = 0;
-    for (uint32_t t = threadIdx.x; t < ns; t += blockDim.x) g_lds_slot[t] = gp<const g_slot>(vm->slots)[t];
-    V.lds_idx = lds_index_load(vm, ns * (uint32_t)(sizeof(DSlot) / 4));
-    V.lds_idx_vm = one;
-    return true;
-}
-
 // Fills the workgroup's copy; entered by every thread.  Returns (uniformly)
 // whether the slots are in LDS.
 __device__ bool lds_slots_load(const DView &V) {
@@ -197,26 +153,12 @@ __device__ bool lds_slots_load(const DView &V) {
 __device__ __forceinline__ DVm load_vm(const DView &V, uint32_t vm, bool lds) {
     DVm v = gp<const DV_GLOBAL DVm>(V.vms)[vm];
     v.lds_base = lds ? g_lds_off[vm] : kLdsNone;
-    v.lds_idx = lds && vm == V.lds_idx_vm ? V.lds_idx : kLdsNone;
     return v;
 }
 
 // GPA -> arena offset (section 4.2: the guest-physical address is turned into
 // the host address backing it, as KVM does with its memslots).
 __device__ __forceinline__ bool slot_lookup(const DVm &v, uint64_t gpa, uint64_t &hpa) {
-    if (v.lds_idx != kLdsNone) {  // the 2 MiB index in LDS: one read unless the block is split
-        const uint64_t blk = gpa >> 21;
-        if (blk < v.index_len) {
-            const uint32_t e = ((const uint32_t *)g_lds_slot)[v.lds_idx + blk];
-            if (e & 2) {
-                hpa = gpa + ((uint64_t)(int64_t)((int32_t)e >> 2) << 12);
-                return true;
-            }
-            if (!(e & 1)) return false;
-        } else if (v.index_complete) {
-            return false;
-        }
-    }
     if (v.lds_base != kLdsNone) {  // binary search of the LDS copy
         const DSlot *sl = g_lds_slot + v.lds_base;
         uint32_t lo = 0, hi = v.nslots;
@@ -1668,225 +1610,393 @@ __global__ void __launch_bounds__(64 * kPlainWaves) k_plain_walk(PlainArgs a) {
         plain_pages<3>(a, vm, sl, sh);
 }
 
-// translate-only: one lane per address
-// The translate-only kernel's record staging area: 64 records of 24 bytes per
-// wavefront, after the walk cache and its owner slots, 16-byte aligned.
-constexpr uint32_t kXlatStage = 64 * 24;
-__host__ __device__ constexpr size_t xlat_stage_off(uint32_t block) {
-    return ((size_t)(block / 64) * kCacheWays * (sizeof(CEnt) + sizeof(uint32_t)) + 15) & ~(size_t)15;
+// ---------------------------------------------------------- translate only
+// One process, one lane per address.  A workgroup keeps in LDS what every
+// address of the process goes through: the VM's guest-physical space as one
+// word per 2 MiB block, and the process's top-level table.  The words of a
+// memslot VM come from the device table; those of a VM with an EPT are made
+// here from its level-2 entries, so that both kinds of VM are looked up alike:
+//   delta / 4 KiB << 2 | 2   the whole block lies at gpa + delta (EPT: readable
+//                            and writable)
+//   pt / 4 KiB << 2 | 3      EPT: a page table at arena offset pt maps the block
+//   1                        search the slots, or walk the EPT
+//   0                        no slot overlaps the block
+//
+// Large calls are bound by HBM (the addresses read and the records written),
+// small ones by the chain of dependent loads.  What stood between a large call
+// and HBM was instructions, about 450 per 64 addresses, half of them table
+// lookups: a region now costs one 16-byte LDS load (its level-2 table already
+// in arena offsets), a table or data page one LDS word, an address without a
+// top-level entry no load at all; the depth and the accessed/dirty variant are
+// template arguments.  4 Mi addresses, 4-level: 68.3 -> 33.7 us (2.5 -> 5.0
+// TB/s of addresses and records); behind an EPT, where each lookup was a walk
+// of four loads, 128.7 -> 39.0; 1000 addresses 6.4 -> 4.9.
+//
+// Accessed/dirty bits: every lane that found a shared entry clear used to
+// issue its own atomic, on one address (a first pass of 4 Mi addresses took
+// 5,960 us against 73 once the bits were set).  The LDS copies of the entries
+// take the bit too, so that each workgroup sets it once: 317 us, then 40.6.
+struct XlatShared {
+    DSlot slots[kSlotRow];
+    uint32_t words[kIndexWords];
+    uint64_t top[512];
+    uint32_t root_code;
+    uint32_t pad[3];
+};
+
+// A 1 GiB region of the process, 16 bytes, read with one LDS load: what the
+// levels above 2 gave.  info as in CEnt (code, level, leaf1g, u, w, abits of
+// levels 4 and 3, dbit); pd: the level-2 table's arena offset, or a 1 GiB
+// leaf's frame.
+constexpr uint32_t kXlatWays = 32;  // regions kept per wavefront
+constexpr uint32_t kXlatNone = 0xFFFFFFFFu;
+struct XlatWave {
+    u32x4 ent[kXlatWays];
+    uint64_t path[2][kXlatWays];  // arena offsets of the level-4 (5-level paging) and level-3 entries
+    uint32_t owner[kXlatWays];
+    uint32_t stage[64 * 6];       // a round's records, written out as contiguous 16-byte chunks
+};
+
+__device__ __forceinline__ uint32_t block_word(int64_t delta) {
+    const int64_t dp = delta >> 12;
+    return dp < -(1ll << 29) || dp >= (1ll << 29) ? 1u : ((uint32_t)(int32_t)dp << 2) | 2u;
 }
 
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) k_xlat(DView v, uint32_t asid,
-                                                                                     const uint64_t *gvas, uint64_t n,
-                                               uint32_t flags, devirt_xlat *out, DCounters *counters) {
-    extern __shared__ __align__(16) uint8_t smem[];
-    const int wave = threadIdx.x >> 6;
-    const int lane = lane_id();
-    CEnt *cache = (CEnt *)smem + wave * kCacheWays;
-    uint32_t *owner = (uint32_t *)((CEnt *)smem + (blockDim.x >> 6) * kCacheWays) + wave * kCacheWays;
-    // the wavefront's 64 records are staged here and written out as
-    // contiguous 16-byte chunks (a record is 24 bytes with sub-dword fields),
-    // with non-temporal stores: nothing on the GPU reads them back soon
-    uint32_t *stage = (uint32_t *)(smem + xlat_stage_off(blockDim.x)) + wave * (kXlatStage / 4);
-    if (lane < kCacheWays) cache[lane].key = ~0ull;
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    const bool valid_asid = asid < v.nproc;
-    DProc p = {0, 0, 4};
-    DVm vmv = {};
-    vmv.lds_base = kLdsNone;
-    vmv.lds_idx = kLdsNone;
-    if (valid_asid) p = gp<const DV_GLOBAL DProc>(v.procs)[asid];
-    const bool lds = valid_asid && lds_slots_load_one(v, p.vm);  // one process: its VM's slots only
-    if (valid_asid) vmv = load_vm(v, p.vm, lds);
-    const uint64_t lim = user_limit(p.levels);
-    const bool write = (flags & DEVIRT_XLAT_WRITE) != 0;
-    const bool set_ad = (flags & DEVIRT_XLAT_SET_AD) != 0;
-    const uint64_t waves = (uint64_t)gridDim.x * (blockDim.x >> 6);
-    unsigned long long hits = 0, misses = 0, atom = 0;
-    // the next round's addresses are loaded at the top of this round
-    const uint64_t first = ((uint64_t)blockIdx.x * (blockDim.x >> 6) + wave) * 64;
-    uint64_t gva_next = first + lane < n ? gp<const g_u64>(gvas)[first + lane] : 0;
-    for (uint64_t b0 = first; b0 < n; b0 += waves * 64) {
-        const uint64_t i = b0 + lane;
-        const bool in = i < n;
-        const uint64_t gva = gva_next;
-        gva_next = i + waves * 64 < n ? gp<const g_u64>(gvas)[i + waves * 64] : 0;
-        devirt_xlat x;
-        x.gpa = 0;
-        x.hpa = 0;
-        x.code = 0;
-        x.level = 0;
-        x.page_shift = 0;
-        x.vm = valid_asid ? (uint16_t)p.vm : (uint16_t)0xFFFF;
-        bool go = in && valid_asid;
-        if (in && !valid_asid) x.code = DEVIRT_INVALID;
-        if (go && gva >= lim) {
-            x.code = DEVIRT_NONCANONICAL;
-            go = false;
-        }
-        CEnt ce;
-        ce.info = 0;
-        ce.path[0] = ce.path[1] = ce.path[2] = 0;
-        ce.base = 0;
-        uint32_t cslot;
-        bool chit;
-        cache_resolve(cache, owner, go, ((uint64_t)asid << 27) | (gva >> 30), vmv, p.cr3, p.levels, gva, ce, cslot,
-                      chit);
-        if (go) {
-            if (chit)
-                hits++;
+// Word of 2 MiB block b of a VM with an EPT (the walk's checks are those of
+// ept_walk; anything but a plain readable and writable mapping is left to it).
+__device__ uint32_t ept_block_word(const DVm &v, uint32_t b) {
+    const auto table = [&](uint64_t e) {
+        return (e & 3) == 3 && !(e & 0xF8) && (e & kAddrMask) < v.arena_bytes &&
+               v.arena_bytes - (e & kAddrMask) >= 4096;
+    };
+    const auto leaf = [&](uint64_t e, uint32_t sh) {
+        const uint64_t mt = (e >> 3) & 7;
+        return (e & 3) == 3 && mt != 2 && mt != 3 && mt != 7 && !(e & ((1ull << sh) - 1) & ~0xFFFull);
+    };
+    const auto whole = [&](uint64_t h) {
+        return h < v.arena_bytes && v.arena_bytes - h >= (1ull << 21) ? block_word((int64_t)(h - ((uint64_t)b << 21)))
+                                                                      : 1u;
+    };
+    const uint64_t e4 = load_entry(v.arena, v.ept_root);
+    if (!table(e4)) return 1;
+    const uint64_t e3 = load_entry(v.arena, (e4 & kAddrMask) + 8 * (b >> 9));
+    if (e3 & 0x80) return leaf(e3, 30) ? whole((e3 & kAddrMask) + ((uint64_t)(b & 511) << 21)) : 1u;
+    if (!table(e3)) return 1;
+    const uint64_t e2 = load_entry(v.arena, (e3 & kAddrMask) + 8 * (b & 511));
+    if (e2 & 0x80) return leaf(e2, 21) ? whole(e2 & kAddrMask) : 1u;
+    if (!table(e2) || (e2 & kAddrMask) >> 42) return 1;
+    return (uint32_t)((e2 & kAddrMask) >> 12) << 2 | 3u;
+}
+
+// GPA -> arena offset as gpa_xlat, through the words in LDS.
+__device__ __forceinline__ uint32_t block_xlat(const DVm &v, const XlatShared &sh, uint32_t nwords, uint64_t gpa,
+                                               uint32_t need, uint64_t &hpa) {
+    const uint64_t blk = gpa >> 21;
+    const uint32_t w = blk < nwords ? sh.words[(uint32_t)blk] : 1u;
+    if ((w & 3) == 2) {
+        hpa = gpa + ((uint64_t)(int64_t)((int32_t)w >> 2) << 12);
+        return DEVIRT_OK;
+    }
+    if (v.ept_root == kNoEpt) {
+        if (w == 0 || (blk >= v.index_len && v.index_complete)) return DEVIRT_NO_MEMSLOT;
+        uint32_t a = 0, b = v.nslots;
+        while (a < b) {
+            const uint32_t mid = (a + b) >> 1;
+            if (sh.slots[mid].gpa <= gpa)
+                a = mid + 1;
             else
-                misses++;
-            uint32_t code = ci_code(ce.info), level = ci_level(ce.info);
-            uint32_t u = ci_u(ce.info), w = ci_w(ce.info), leaf_level = 0, shift = 0;
-            uint64_t frame = 0, pde_off = 0, pte_off = 0, e2 = 0, e1 = 0;
+                b = mid;
+        }
+        if (a == 0 || gpa >= sh.slots[a - 1].end) return DEVIRT_NO_MEMSLOT;
+        hpa = sh.slots[a - 1].arena_off + (gpa - sh.slots[a - 1].gpa);
+        return DEVIRT_OK;
+    }
+    if (w & 2) {  // the EPT's page table is known
+        const uint64_t e = load_entry(v.arena, ((uint64_t)(w >> 2) << 12) + 8 * ((gpa >> 12) & 511));
+        const uint64_t mt = (e >> 3) & 7, pg = e & kAddrMask;
+        if (!(e & 7)) return DEVIRT_EPT_VIOLATION;
+        if ((e & 3) == 2 || mt == 2 || mt == 3 || mt == 7 || pg >= v.arena_bytes || v.arena_bytes - pg < 4096)
+            return DEVIRT_EPT_MISCONFIG;
+        if (need & ~(uint32_t)e & 3) return DEVIRT_EPT_VIOLATION;
+        hpa = pg | (gpa & 0xFFF);
+        return DEVIRT_OK;
+    }
+    const XRes r = ept_walk(v.arena, v.arena_bytes, v.ept_root, gpa, need);
+    if (r.code == DEVIRT_OK) hpa = r.hpa;
+    return r.code;
+}
+
+__host__ __device__ constexpr size_t xlat_lds(uint32_t block) {
+    return sizeof(XlatShared) + (size_t)(block / 64) * sizeof(XlatWave);
+}
+
+// The levels above 2 of one address (miss path), from the top entry in LDS.
+template <int LEVELS>
+__device__ __forceinline__ void xlat_upper(const XlatArgs &a, const DVm &vm, const XlatShared &sh, uint32_t nwords,
+                                           uint64_t gva, uint32_t &info, uint64_t &pd, uint64_t (&path)[2]) {
+    uint32_t u = 1, w = 1, abits = 0, dbit = 0, xc = sh.root_code;
+    uint64_t e = LEVELS == 3 ? sh.top[(gva >> 30) & 3] : sh.top[(gva >> (12 + 9 * (LEVELS - 1))) & 511];
+    pd = path[0] = path[1] = 0;
+#pragma unroll
+    for (int lvl = LEVELS; lvl >= 3; --lvl) {
+        if (xc) {
+            info = xc | ((uint32_t)lvl << 4);
+            return;
+        }
+        if (lvl < LEVELS) {
+            uint64_t th;
+            xc = block_xlat(vm, sh, nwords, e & kAddrMask, kNeedTable, th);
+            if (xc) {
+                info = xc | ((uint32_t)lvl << 4);
+                return;
+            }
+            path[4 - lvl] = th + 8 * ((gva >> (12 + 9 * (lvl - 1))) & 511);
+            e = load_entry(vm.arena, path[4 - lvl]);
+            if (e & kA) abits |= 1u << (4 - lvl);
+        }
+        if (!(e & kP)) {
+            info = DEVIRT_NOT_PRESENT | ((uint32_t)lvl << 4);
+            return;
+        }
+        if (LEVELS == 3) {
+            if (e & kPaeRootRsvd) {
+                info = DEVIRT_RESERVED | (3u << 4);
+                return;
+            }
+        } else {
+            u &= (uint32_t)(e >> 2) & 1u;
+            w &= (uint32_t)(e >> 1) & 1u;
+            if ((e & kPS) && (lvl >= 4 || (e & 0x3FFFE000ull))) {  // bits 29:13 of a 1 GiB leaf are reserved
+                info = DEVIRT_RESERVED | ((uint32_t)lvl << 4);
+                return;
+            }
+            if (lvl == 3 && (e & kPS)) {
+                pd = e & kAddrMask & ~((1ull << 30) - 1);
+                dbit = (e & kD) ? kCiDbit : 0u;
+                info = (1u << 8) | (u << 9) | (w << 10) | (abits << 13) | dbit;
+                return;
+            }
+        }
+    }
+    xc = block_xlat(vm, sh, nwords, e & kAddrMask, kNeedTable, pd);
+    info = xc ? xc | (2u << 4) : (u << 9) | (w << 10) | (abits << 13);
+}
+
+template <int LEVELS, bool AD>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(AD ? 6 : 8))) k_xlat(XlatArgs a) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    XlatShared &sh = *(XlatShared *)smem;
+    const int lane = lane_id();
+    XlatWave &wv = *(XlatWave *)(smem + sizeof(XlatShared) + (threadIdx.x >> 6) * sizeof(XlatWave));
+    const bool write = (a.flags & DEVIRT_XLAT_WRITE) != 0;
+    const DVm vm = load_vm(a.v, a.vm, false);
+    typedef DV_GLOBAL DSlot g_slot;
+    const g_slot *row = gp<const g_slot>(a.v.slots) + (uint64_t)a.vm * kSlotRow;
+    if (threadIdx.x < kSlotRow) sh.slots[threadIdx.x] = row[threadIdx.x];
+    uint32_t nwords = vm.nwords;
+    if (vm.ept_root == kNoEpt) {
+        for (uint32_t t = threadIdx.x; t < nwords; t += blockDim.x) sh.words[t] = gp<const g_u32>(vm.words)[t];
+    } else {
+        const uint64_t nb = (vm.arena_bytes + (1ull << 21) - 1) >> 21;
+        nwords = nb < kIndexWords ? (uint32_t)nb : kIndexWords;
+        for (uint32_t t = threadIdx.x; t < nwords; t += blockDim.x) sh.words[t] = ept_block_word(vm, t);
+    }
+    if (lane < (int)kXlatWays) wv.ent[lane] = (u32x4){kXlatNone, 0u, 0u, 0u};
+    __syncthreads();
+    uint64_t root = 0;  // the top-level table's arena offset
+    const uint32_t root_code = block_xlat(vm, sh, nwords, LEVELS == 3 ? (a.cr3 & 0xFFFFFFE0ull) : (a.cr3 & kAddrMask),
+                                          kNeedTable, root);
+    if (threadIdx.x == 0) sh.root_code = root_code;
+    if (!root_code)
+        for (uint32_t t = threadIdx.x; t < (LEVELS == 3 ? 4u : 512u); t += blockDim.x)
+            sh.top[t] = load_entry(vm.arena, root + 8 * t);
+    __syncthreads();
+    const uint64_t lim = user_limit(LEVELS);
+    const uint64_t waves = (uint64_t)gridDim.x * (blockDim.x >> 6);
+    uint32_t hits = 0, misses = 0, atom = 0;
+    // the next round's addresses are loaded at the top of this round
+    const uint64_t first = ((uint64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 64;
+    uint64_t gva_next = first + lane < a.n ? gp<const g_u64>(a.gva)[first + lane] : 0;
+    for (uint64_t b0 = first; b0 < a.n; b0 += waves * 64) {
+        const uint64_t gva = gva_next, i = b0 + lane;
+        gva_next = i + waves * 64 < a.n ? gp<const g_u64>(a.gva)[i + waves * 64] : 0;
+        const bool go = i < a.n && gva < lim;
+        uint32_t code = DEVIRT_NONCANONICAL, level = 0, shift = 0, leaf = 0;
+        uint64_t gpa = 0, hpa = 0, e2 = 0, e1 = 0, pde_off = 0, pte_off = 0;
+        // ---- the levels above 2
+        const uint32_t key = (uint32_t)(gva >> 30);
+        const uint32_t slot = (key ^ (key >> 5) ^ (key >> 10)) & (kXlatWays - 1);
+        const u32x4 ent = wv.ent[slot];
+        uint32_t info = ent.y;
+        uint64_t pd = ((uint64_t)ent.w << 32) | ent.z;
+        const bool miss = go && ent.x != key;
+        if (a.counters) {
+            hits += go && !miss;
+            misses += miss;
+        }
+        uint64_t path[2] = {0, 0};
+        if (AD && LEVELS > 3) {
+            path[0] = wv.path[0][slot];
+            path[1] = wv.path[1][slot];
+        }
+        if (__ballot(miss)) {
+            if (miss) xlat_upper<LEVELS>(a, vm, sh, nwords, gva, info, pd, path);
+            // an address without a top-level entry leaves the region its slot holds alone
+            const bool keep = miss && !(ci_code(info) && ci_level(info) == (uint32_t)LEVELS);
+            if (keep) wv.owner[slot] = (uint32_t)lane;
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (keep && wv.owner[slot] == (uint32_t)lane) {
+                wv.ent[slot] = (u32x4){key, info, (uint32_t)pd, (uint32_t)(pd >> 32)};
+                if (AD) {
+                    wv.path[0][slot] = path[0];
+                    wv.path[1][slot] = path[1];
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+        if (go) {
+            uint32_t u = ci_u(info), w = ci_w(info);
+            code = ci_code(info);
+            level = ci_level(info);
+            uint64_t frame = pd;
             if (code == 0) {
-                if (ci_leaf(ce.info)) {
-                    frame = ce.base;
-                    shift = 30;
-                    leaf_level = 3;
-                } else {
-                    uint64_t th;
-                    const uint32_t xc = gpa_xlat(vmv, ce.base, kNeedTable, th);
-                    if (xc) {
-                        code = xc;
+                leaf = 3;
+                if (!ci_leaf(info)) {
+                    pde_off = pd + 8 * ((gva >> 21) & 511);
+                    e2 = load_entry(vm.arena, pde_off);
+                    if (!(e2 & kP)) {
+                        code = DEVIRT_NOT_PRESENT;
+                        level = 2;
+                    } else if ((LEVELS == 3 && (e2 & kPaeRsvd)) || ((e2 & kPS) && (e2 & 0x1FE000ull))) {
+                        code = DEVIRT_RESERVED;  // bits 20:13 of a 2 MiB leaf
                         level = 2;
                     } else {
-                        pde_off = th + 8 * ((gva >> 21) & 511);
-                        e2 = load_entry(vmv.arena, pde_off);
-                        if (!(e2 & kP)) {
-                            code = DEVIRT_NOT_PRESENT;
-                            level = 2;
-                        } else if (p.levels == 3 && (e2 & kPaeRsvd)) {
-                            code = DEVIRT_RESERVED;
-                            level = 2;
-                        } else {
-                            u &= (uint32_t)(e2 >> 2) & 1u;
-                            w &= (uint32_t)(e2 >> 1) & 1u;
-                            if (e2 & kPS) {
-                                if (e2 & 0x1FE000ull) {
+                        u &= (uint32_t)(e2 >> 2) & 1u;
+                        w &= (uint32_t)(e2 >> 1) & 1u;
+                        leaf = 2;
+                        frame = e2 & kAddrMask & ~((1ull << 21) - 1);
+                        if (!(e2 & kPS)) {
+                            uint64_t pt;
+                            code = block_xlat(vm, sh, nwords, e2 & kAddrMask, kNeedTable, pt);
+                            level = 1;
+                            if (!code) {
+                                pte_off = pt + 8 * ((gva >> 12) & 511);
+                                e1 = load_entry(vm.arena, pte_off);
+                                if (!(e1 & kP)) {
+                                    code = DEVIRT_NOT_PRESENT;
+                                } else if (LEVELS == 3 && (e1 & kPaeRsvd)) {
                                     code = DEVIRT_RESERVED;
-                                    level = 2;
                                 } else {
-                                    frame = e2 & kAddrMask & ~((1ull << 21) - 1);
-                                    shift = 21;
-                                    leaf_level = 2;
-                                }
-                            } else {
-                                uint64_t pt;
-                                const uint32_t xc1 = gpa_xlat(vmv, e2 & kAddrMask, kNeedTable, pt);
-                                if (xc1) {
-                                    code = xc1;
-                                    level = 1;
-                                } else {
-                                    pte_off = pt + 8 * ((gva >> 12) & 511);
-                                    e1 = load_entry(vmv.arena, pte_off);
-                                    if (!(e1 & kP)) {
-                                        code = DEVIRT_NOT_PRESENT;
-                                        level = 1;
-                                    } else if (p.levels == 3 && (e1 & kPaeRsvd)) {
-                                        code = DEVIRT_RESERVED;
-                                        level = 1;
-                                    } else {
-                                        u &= (uint32_t)(e1 >> 2) & 1u;
-                                        w &= (uint32_t)(e1 >> 1) & 1u;
-                                        frame = e1 & kAddrMask;
-                                        shift = 12;
-                                        leaf_level = 1;
-                                    }
+                                    u &= (uint32_t)(e1 >> 2) & 1u;
+                                    w &= (uint32_t)(e1 >> 1) & 1u;
+                                    leaf = 1;
+                                    level = 0;
+                                    frame = e1 & kAddrMask;
                                 }
                             }
                         }
                     }
                 }
             }
-            uint64_t gpa = 0, hpa = 0;
             if (code == 0) {
+                shift = 3 + 9 * leaf;
                 gpa = frame | (gva & ((1ull << shift) - 1));
-                x.gpa = gpa;
-                x.page_shift = (uint8_t)shift;
                 if (!u) {
                     code = DEVIRT_PROT_USER;
-                    level = leaf_level;
+                    level = leaf;
                 } else if (write && !w) {
                     code = DEVIRT_PROT_WRITE;
-                    level = leaf_level;
+                    level = leaf;
                 } else {
-                    const uint32_t xc = gpa_xlat(vmv, gpa, write ? kNeedW : kNeedR, hpa);
-                    if (xc) {
-                        code = xc;
-                        level = 0;
-                        hpa = 0;
+                    level = 0;
+                    code = block_xlat(vm, sh, nwords, gpa, write ? kNeedW : kNeedR, hpa);
+                    if (code) hpa = 0;
+                }
+            }
+        }
+        if (AD) {
+            // A and D of the path.  The shared levels are set once: the LDS
+            // copy of the entry takes the bit too, and only the lane that finds
+            // it clear there goes to memory; of neighbouring lanes with one
+            // level-2 entry the first sets it.
+            const bool ok = go && code == 0;
+            const uint64_t prev_off = shfl64(pde_off, lane > 0 ? lane - 1 : 0);
+            const bool prev_ok = shfl32(ok ? 1u : 0u, lane > 0 ? lane - 1 : 0) != 0 && lane > 0;
+            if (ok && LEVELS > 3) {
+                const uint32_t ti = (uint32_t)(gva >> (12 + 9 * (LEVELS - 1))) & 511u;
+                uint32_t *top = (uint32_t *)&sh.top[ti];
+                if (!(*(volatile uint32_t *)top & (uint32_t)kA) && !(atomicOr(top, (uint32_t)kA) & (uint32_t)kA)) {
+                    or_entry(vm.arena, root + 8 * ti, (uint32_t)kA);
+                    atom++;
+                }
+                uint32_t *cached = (uint32_t *)&wv.ent[slot] + 1;
+                const bool mine = ((uint32_t *)&wv.ent[slot])[0] == key;
+#pragma unroll
+                for (int lvl = LEVELS - 1; lvl >= 3; --lvl) {
+                    uint32_t have = 1u << (17 - lvl), want = (uint32_t)kA;  // info bit of the level's accessed bit
+                    if (lvl == 3 && leaf == 3 && write) {
+                        have |= kCiDbit;
+                        want |= (uint32_t)kD;
+                    }
+                    if ((info & have) != have && (!mine || (atomicOr(cached, have) & have) != have)) {
+                        or_entry(vm.arena, path[4 - lvl], want);
+                        atom++;
                     }
                 }
             }
-            x.code = code;
-            x.level = (uint8_t)level;
-            if (code == 0) {
-                x.hpa = hpa;
-                if (set_ad) {
-                    const uint32_t np = ci_np(ce.info), ab = ci_abits(ce.info);
-#pragma unroll
-                    for (int q = 0; q < 3; ++q) {
-                        if ((uint32_t)q >= np) continue;
-                        uint32_t want = (uint32_t)kA;
-                        bool need = !((ab >> q) & 1u);
-                        if (leaf_level == 3 && (uint32_t)q + 1 == np && write) {
-                            want |= (uint32_t)kD;
-                            need = need || !(ce.info & kCiDbit);
-                        }
-                        if (need) {
-                            or_entry(vmv.arena, ce.path[q], want);
-                            atom++;
-                        }
-                    }
-                    if (leaf_level <= 2) {
-                        uint32_t want = (uint32_t)kA | ((leaf_level == 2 && write) ? (uint32_t)kD : 0u);
-                        if (((uint32_t)e2 & want) != want) {
-                            or_entry(vmv.arena, pde_off, want);
-                            atom++;
-                        }
-                    }
-                    if (leaf_level == 1) {
-                        uint32_t want = (uint32_t)kA | (write ? (uint32_t)kD : 0u);
-                        if (((uint32_t)e1 & want) != want) {
-                            or_entry(vmv.arena, pte_off, want);
-                            atom++;
-                        }
-                    }
+            if (ok && leaf <= 2) {
+                const uint32_t want = (uint32_t)kA | ((leaf == 2 && write) ? (uint32_t)kD : 0u);
+                if (((uint32_t)e2 & want) != want && !(prev_ok && prev_off == pde_off)) {
+                    or_entry(vm.arena, pde_off, want);
+                    atom++;
+                }
+            }
+            if (ok && leaf == 1) {
+                const uint32_t want = (uint32_t)kA | (write ? (uint32_t)kD : 0u);
+                if (((uint32_t)e1 & want) != want) {
+                    or_entry(vm.arena, pte_off, want);
+                    atom++;
                 }
             }
         }
         // every lane stages its record (an idle lane's is never written out)
         {
-            uint32_t *r = stage + 6 * lane;
-            *(uint64_t *)r = x.gpa;
-            *(uint64_t *)(r + 2) = x.hpa;
-            r[4] = x.code;
-            r[5] = (uint32_t)x.level | ((uint32_t)x.page_shift << 8) | ((uint32_t)x.vm << 16);
+            uint32_t *r = wv.stage + 6 * lane;
+            *(uint64_t *)r = gpa;
+            *(uint64_t *)(r + 2) = hpa;
+            r[4] = code;
+            r[5] = level | (shift << 8) | (a.vm << 16);
         }
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();
         {
-            const uint32_t valid = 24u * (uint32_t)(n - b0 < 64 ? n - b0 : 64);  // bytes of this round
-            uint8_t *dst = (uint8_t *)out + 24 * b0;
+            const uint32_t valid = 24u * (uint32_t)(a.n - b0 < 64 ? a.n - b0 : 64);  // bytes of this round
+            uint8_t *dst = (uint8_t *)a.out + 24 * b0;
 #pragma unroll
             for (uint32_t k = 0; k < 2; ++k) {
                 const uint32_t c = (uint32_t)lane + 64u * k;  // 16-byte chunk of the round
                 if (16u * c + 16u <= valid)
-                    __builtin_nontemporal_store(*(const u32x4 *)(stage + 4 * c), gp<g_u32x4_w4>(dst + 16 * c));
+                    __builtin_nontemporal_store(*(const u32x4 *)(wv.stage + 4 * c), gp<g_u32x4_w4>(dst + 16 * c));
                 else if (16u * c < valid)  // the last 8 bytes of an odd count
-                    __builtin_nontemporal_store(*(const uint64_t *)(stage + 4 * c), gp<g_u64>(dst + 16 * c));
+                    __builtin_nontemporal_store(*(const uint64_t *)(wv.stage + 4 * c), gp<g_u64>(dst + 16 * c));
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();
     }
-    if (counters) {
+    if (a.counters) {
         GroupOut st = {0, hits, misses, 0, 0, atom, 0};
-        flush_counters(counters, st);
+        flush_counters(a.counters, st);
     }
+}
+
+// The records of an unknown process.
+__global__ void __launch_bounds__(256) k_xlat_unknown(XlatArgs a) {
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.n; i += stride)
+        gp<DV_GLOBAL devirt_xlat>(a.out)[i] = devirt_xlat{0, 0, DEVIRT_INVALID, 0, 0, 0xFFFF};
 }
 
 // ------------------------------------------------------------ fault list
@@ -2013,10 +2123,16 @@ hipError_t launch_plain(hipStream_t s, DView v, DBatch b, devirt_request req, in
     return hipGetLastError();
 }
 
-hipError_t launch_xlat(hipStream_t s, int grid, int block, DView v, uint32_t asid, const uint64_t *gva, uint64_t n,
-                       uint32_t flags, devirt_xlat *out, DCounters *counters) {
-    hipLaunchKernelGGL(k_xlat, dim3(grid), dim3(block), xlat_stage_off(block) + (size_t)(block / 64) * kXlatStage, s, v,
-                       asid, gva, n, flags, out, counters);
+hipError_t launch_xlat(hipStream_t s, int grid, int block, const XlatArgs &a) {
+    void (*k)(XlatArgs) = k_xlat_unknown;
+    const bool ad = (a.flags & DEVIRT_XLAT_SET_AD) != 0;
+    if (a.levels == 5)
+        k = ad ? k_xlat<5, true> : k_xlat<5, false>;
+    else if (a.levels == 4)
+        k = ad ? k_xlat<4, true> : k_xlat<4, false>;
+    else if (a.levels == 3)
+        k = ad ? k_xlat<3, true> : k_xlat<3, false>;
+    hipLaunchKernelGGL(k, dim3(grid), dim3(a.levels ? block : 256), a.levels ? xlat_lds(block) : 0, s, a);
     return hipGetLastError();
 }
 

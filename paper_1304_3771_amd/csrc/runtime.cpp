@@ -207,8 +207,10 @@ static int upload_vms(devirt_ctx *c, size_t changed) {
         h[i].nslots = v.nsorted;
         h[i].index_complete = v.index_complete;
         h[i].lds_base = kLdsNone;
-        h[i].lds_idx = kLdsNone;
         h[i].ept_root = v.ept_root;
+        h[i].words = (const uint32_t *)(v.d_index + v.index_len);
+        h[i].nwords = v.nwords;
+        h[i].pad = 0;
     }
     if (!h.empty()) HIPCHK(hipMemcpy(c->d_vms, h.data(), h.size() * sizeof(DVm), hipMemcpyHostToDevice));
     c->tables_version++;
@@ -356,7 +358,16 @@ extern "C" int devirt_memslot_set(devirt_ctx *c, uint32_t vm, uint32_t slot, uin
     uint32_t complete = 1;
     build_slot_index(nv, sorted, index, complete);
     uint64_t *di = nullptr;
-    if (!index.empty()) {
+    const size_t nblk = index.size(), nwords = std::min<size_t>(nblk, kIndexWords);
+    if (nblk) {
+        index.resize(nblk + (nwords + 1) / 2);
+        uint32_t *words = (uint32_t *)(index.data() + nblk);
+        for (size_t b = 0; b < nwords; ++b) {
+            const int64_t dp = (int64_t)(index[b] & ~0xFFFull) >> 12;
+            words[b] = !(index[b] & 2)                                ? (uint32_t)index[b]
+                       : dp < -(1ll << 29) || dp >= (1ll << 29) ? 1u
+                                                                : (uint32_t)((uint64_t)dp << 2) | 2u;
+        }
         if (hipMalloc(&di, index.size() * 8) != hipSuccess) return dv_fail(-ENOMEM, "hipMalloc slot index");
         HIPCHK(hipMemcpy(di, index.data(), index.size() * 8, hipMemcpyHostToDevice));
     }
@@ -364,7 +375,8 @@ extern "C" int devirt_memslot_set(devirt_ctx *c, uint32_t vm, uint32_t slot, uin
     v = nv;
     v.d_index = di;
     v.nsorted = (uint32_t)sorted.size();
-    v.index_len = (uint32_t)index.size();
+    v.index_len = (uint32_t)nblk;
+    v.nwords = (uint32_t)nwords;
     v.index_complete = complete;
     return upload_vms(c, vm);
 }
@@ -408,8 +420,6 @@ DView view_of(const devirt_ctx *c) {
     v.nvm = (uint32_t)c->vms.size();
     v.nproc = (uint32_t)c->procs.size();
     v.lds = 0;
-    v.lds_idx = kLdsNone;
-    v.lds_idx_vm = kLdsNone;
     v.pad = 0;
     return v;
 }
@@ -768,13 +778,30 @@ extern "C" int devirt_translate(devirt_ctx *c, uint32_t asid, const uint64_t *gv
     if (!gva_dev || !out_dev) return dv_fail(-EINVAL, "NULL buffer");
     if (set_dev(c)) return -EIO;
     hipStream_t s = (hipStream_t)stream;
-    const uint32_t block = 256;
-    int grid = grid_for(c, (n + 63) / 64, block, 8);
+    XlatArgs a;
+    memset(&a, 0, sizeof a);
+    a.v = view_of(c);
+    a.gva = gva_dev;
+    a.n = n;
+    a.flags = flags;
+    a.out = out_dev;
+    a.counters = (c->profiling & DEVIRT_PROF_COUNTERS) ? c->d_counters : nullptr;
+    if (asid < c->procs.size()) {
+        a.vm = c->procs[asid].vm;
+        a.cr3 = c->procs[asid].cr3;
+        a.levels = c->procs[asid].levels;
+    }
+    // A workgroup fills its own copy of the block words and of the top-level
+    // table.  Four of 8 wavefronts fill a CU (three where the accessed/dirty
+    // variant's registers allow 7 wavefronts a SIMD: with a fourth waiting for
+    // a free place 4 Mi addresses took 50.2 us, not 40.6); what does not fill
+    // those spreads over twice as many workgroups of half the size.
+    const uint32_t per_cu = (flags & DEVIRT_XLAT_SET_AD) ? 3 : 4;
+    const uint32_t block = n > 768ull * c->cus ? 512 : 256;
     ProfEv *pe;
     int rc = prof_begin(c, s, 1, &pe);
     if (rc) return rc;
-    HIPCHK(launch_xlat(s, grid, block, view_of(c), asid, gva_dev, n, flags, out_dev,
-                       (c->profiling & DEVIRT_PROF_COUNTERS) ? c->d_counters : nullptr));
+    HIPCHK(launch_xlat(s, grid_for(c, (n + 63) / 64, block, per_cu), block, a));
     return prof_end(c, s, pe);
 }
 

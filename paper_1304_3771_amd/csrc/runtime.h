@@ -15,8 +15,8 @@ struct VmHost {
         uint64_t gpa = 0, bytes = 0, off = 0;
         bool used = false;
     } slots[64];
-    uint64_t *d_index = nullptr;
-    uint32_t index_len = 0, nsorted = 0, index_complete = 1;
+    uint64_t *d_index = nullptr;  // index_len entries, then nwords 32-bit words
+    uint32_t index_len = 0, nwords = 0, nsorted = 0, index_complete = 1;
     uint64_t ept_root = ~0ull;  // ~0: translate through the memslots
 };
 
