@@ -99,8 +99,10 @@ constexpr uint32_t kLineWords = 32;
 // translating wavefront or, when that wavefront may run during an earlier
 // epoch's copies, left to the epoch's spill pass (DBatch::spill_mode).
 struct DEpochCtr {
-    uint32_t group_cursor;  // groups claimed beyond each wavefront's first
-    uint32_t pad[kLineWords - 1];
+    // groups claimed beyond each wavefront's first: the wavefronts of part p
+    // (their index mod the number of parts) share cursor[p] and the groups p,
+    // p + parts, p + 2 parts, ... after those first ones
+    uint32_t cursor[kQParts][kLineWords];
     // segments in part p of the long queue (q[p]) and of the short queue
     // (q[kQParts + p])
     uint32_t q[2 * kQParts][kLineWords];
