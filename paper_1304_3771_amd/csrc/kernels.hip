@@ -1244,18 +1244,26 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) 
     const int lane = lane_id();
     const uint64_t pcap = b.part_cap;
     // lane p < 32: part p of the long queue; lane 32 + p: part p of the short
-    // queue.  Exclusive scan of the part counts within each half.
-    uint32_t cnt = b.ctr[epoch].q[lane][0];
-    if (cnt > pcap) cnt = (uint32_t)pcap;
-    uint32_t incl = cnt;
+    // queue.  Exclusive scan of the part counts within each half, by the
+    // workgroup's first wavefront for all of them: every count is a line of
+    // its own, and a wavefront copies only a few segments.
+    __shared__ uint32_t s_excl[64], s_n[2];
+    if (threadIdx.x < 64) {
+        uint32_t cnt = b.ctr[epoch].q[lane][0];
+        if (cnt > pcap) cnt = (uint32_t)pcap;
+        uint32_t incl = cnt;
 #pragma unroll
-    for (int d = 1; d < 32; d <<= 1) {
-        const uint32_t t = shfl32(incl, (lane & 31) >= d ? lane - d : lane);
-        if ((lane & 31) >= d) incl += t;
+        for (int d = 1; d < 32; d <<= 1) {
+            const uint32_t t = shfl32(incl, (lane & 31) >= d ? lane - d : lane);
+            if ((lane & 31) >= d) incl += t;
+        }
+        s_excl[lane] = incl - cnt;
+        if ((lane & 31) == 31) s_n[lane >> 5] = incl;
     }
-    const uint32_t excl = incl - cnt;
-    const uint32_t nlong = uniform_u32(shfl32(incl, 31));
-    const uint32_t nshort = uniform_u32(shfl32(incl, 63));
+    __syncthreads();
+    const uint32_t excl = s_excl[lane];
+    const uint32_t nlong = uniform_u32(s_n[0]);
+    const uint32_t nshort = uniform_u32(s_n[1]);
     const bool lo_half = lane < 32;
     // queue index s lies in the last part whose exclusive start is <= s
     // (parts are in lane order, so those lanes form a prefix of the half)
