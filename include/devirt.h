@@ -347,7 +347,8 @@ typedef struct {
     uint32_t inline_bytes;    /* segments up to this size (<= 256) are copied by the
                                  translating lane itself                            */
     uint32_t use_graph;       /* 1: capture each distinct batch shape as a HIP graph
-                                 and replay it                                     */
+                                 and replay it (a batch of one epoch without
+                                 completion times is two launches and needs none)  */
     uint32_t overlap;         /* 1: translate epoch e+1 on a second stream while
                                  epoch e is being copied                          */
     uint32_t fifo_entries;    /* per-request path: entries of each process's FIFO

@@ -189,6 +189,17 @@ struct DBatch {
     uint32_t pad1;
 };
 
+// What the copy launch of a one-epoch batch does besides: a workgroup of its
+// own (the first) builds the fault list of at most kTailFaults requests, and
+// clears the counters that the stream's next such batch will use.
+constexpr uint64_t kTailFaults = 16384;
+struct CopyTail {
+    uint64_t n;            // requests (0: no such workgroup)
+    devirt_fault *faults;  // may be null
+    uint64_t *n_faults;    // may be null
+    DEpochCtr *clear;
+};
+
 // One per-request copy (k_plain_walk).  What the process id names is fixed
 // when the process is created, so it is passed by value; the VM's record, its
 // memslots and its EPT root are read from the device tables.
@@ -231,7 +242,7 @@ hipError_t launch_translate_groups(hipStream_t s, int grid, int block, DView v, 
                                    uint64_t r1, uint32_t epoch, int direct);
 hipError_t launch_translate_large(hipStream_t s, int grid, int block, DView v, DBatch b, uint64_t r0,
                                   uint32_t epoch);
-hipError_t launch_copy(hipStream_t s, int grid, int block, DBatch b, uint32_t epoch);
+hipError_t launch_copy(hipStream_t s, int grid, int block, DBatch b, uint32_t epoch, const CopyTail &tail = {});
 hipError_t launch_spill(hipStream_t s, int grid, int block, DView v, DBatch b, uint64_t r0, uint64_t r1,
                         uint32_t epoch);
 hipError_t launch_plain_walk(hipStream_t s, uint32_t waves, const PlainArgs &a);

@@ -35,8 +35,13 @@ struct Workspace {
     uint64_t seg_cap = 0;
     dv::DSeg *shorts = nullptr;  // short-segment queue, same capacity
     uint64_t short_cap = 0;
+    // epoch counters: two sets for one-epoch batches, used in turn (each such
+    // batch leaves the other set clear for the next), then, from kCtrShared, the
+    // ones every other call clears for itself
     dv::DEpochCtr *ctr = nullptr;
     uint64_t ctr_cap = 0;
+    uint32_t ctr_turn = 0;
+    bool ctr_clear = false;      // set ctr_turn is clear once the stream gets there
     uint32_t *pending = nullptr;
     uint64_t pending_cap = 0;
     uint32_t *tiles = nullptr;
@@ -58,6 +63,8 @@ struct Workspace {
     hipEvent_t map_ev = nullptr;        // the last pool upload
     ~Workspace();
 };
+
+constexpr uint64_t kCtrShared = 2;
 
 struct ProfEv {
     int kind;  // 0 copy, 1 translate
@@ -98,6 +105,7 @@ struct BatchArgs {
     uint64_t *t_done = nullptr;
     std::vector<uint64_t> epochs;
     bool direct = false;  // one translate launch that also copies (small batches)
+    bool captured = false;  // the caller is capturing the stream
 };
 
 // Device memory of the per-request copy that allocates nothing: one

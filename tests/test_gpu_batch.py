@@ -29,3 +29,93 @@ def test_groups_beyond_the_first_ones(group, n):
         assert st["pages_walked"] > 0.9 * n and st["ad_atomics"] == 0
     finally:
         ctx.close()
+
+
+def _run(ctx, dw, n, ends, faults=True, reps=1, stream=None):
+    import torch
+    import paper_1304_3771_amd as dv
+    res = torch.zeros(max(n, 1) * 24, dtype=torch.uint8, device="cuda")
+    fl = torch.full((max(n, 1) * 24,), 0x5A, dtype=torch.uint8, device="cuda") if faults else None
+    nf = torch.full((1,), -1, dtype=torch.int64, device="cuda") if faults else None
+    torch.cuda.synchronize()
+    for _ in range(reps):
+        ctx.submit_batch(dw.reqs, n, res, ends, fl, nf, stream=stream)
+    ctx.sync(stream)
+    k = int(nf.item()) if faults else 0
+    if faults:
+        assert bool((fl[k * 24:] == 0x5A).all()), "written past the fault list"
+    return (res.cpu().numpy()[:n * 24].view(dv.RESULT_DTYPE),
+            fl.cpu().numpy()[:k * 24].view(dv.FAULT_DTYPE) if faults else None)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("copy_wg", [64, 512, 1024])
+def test_one_epoch_batches(copy_wg):
+    """One-epoch batches of the sizes at the edges of the fault list's passes and of its limit, back to back on
+    one stream (each clears the counters of the next), between a multi-epoch batch and per-request copies."""
+    import torch  # noqa: F401
+    sp = gen.spec("C1", mem_bytes=64 * MiB, n_requests=17000, len_lo=8, len_hi=200, p_np=0.3, rho=0.9, seed=4600)
+    w = gen.make_workload(sp)
+    assert len(w.epoch_end) == 1
+    exp = oracle_batch(w)
+    ctx = new_ctx(copy_wg=copy_wg)
+    try:
+        dw = device.load(ctx, w)
+        for n in (1, 63, 64, 65, 511, 513, 1024, 8191, 8192, 8193, 16384, 16385, 17000, 256):
+            r, f = _run(ctx, dw, n, None)
+            e = exp[1][exp[1]["req_index"] < n]
+            log(f"copy_wg {copy_wg}: {n} requests, {len(f)} faults")
+            assert np.array_equal(r, exp[0][:n]) and np.array_equal(f, e), n
+            if n == 65:  # other users of the stream's counters
+                _run(ctx, dw, 4000, np.array([1000, 1000, 4000], np.uint64))
+                q = dw.reqs_host[0]
+                res = torch.zeros(24, dtype=torch.uint8, device="cuda")
+                ctx.copy_from_guest(0, int(w.procs[0].vmas[0][0]), int(dw.pool.data_ptr()), 300000, res)
+                del q
+                dw.pool.copy_(torch.from_numpy(w.pool_image()))
+            if n == 513:
+                _run(ctx, dw, n, None, faults=False)
+        got = (*_run(ctx, dw, 17000, None), device.read_arenas(ctx, dw), dw.pool.cpu().numpy())
+        assert compare("one epoch", got, exp) == []
+    finally:
+        ctx.close()
+
+
+@pytest.mark.gpu
+def test_one_epoch_batch_under_capture():
+    """A caller's own capture of a one-epoch batch, replayed between eager ones."""
+    import torch
+    sp = gen.spec("C1", mem_bytes=64 * MiB, n_requests=3000, len_lo=8, len_hi=400, p_np=0.2, rho=0.9, seed=4601)
+    w = gen.make_workload(sp)
+    exp = oracle_batch(w)
+    ctx = new_ctx()
+    try:
+        dw = device.load(ctx, w)
+        st = torch.cuda.Stream()
+        n = dw.n
+        import paper_1304_3771_amd as dv
+        res = torch.zeros(n * 24, dtype=torch.uint8, device="cuda")
+        fl = torch.zeros(n * 24, dtype=torch.uint8, device="cuda")
+        nf = torch.zeros(1, dtype=torch.int64, device="cuda")
+        torch.cuda.synchronize()
+        ctx.submit_batch(dw.reqs, n, res, None, fl, nf, stream=st)  # sizes the workspace
+        ctx.sync(st)
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=st):
+            ctx.submit_batch(dw.reqs, n, res, None, fl, nf, stream=st)
+        for k in range(6):
+            res.zero_(), fl.zero_(), nf.zero_()
+            torch.cuda.synchronize()
+            if k % 2:
+                with torch.cuda.stream(st):
+                    g.replay()
+            else:
+                ctx.submit_batch(dw.reqs, n, res, None, fl, nf, stream=st)
+            ctx.sync(st)
+            torch.cuda.synchronize()
+            m = int(nf.item())
+            got = (res.cpu().numpy().view(dv.RESULT_DTYPE), fl.cpu().numpy()[:m * 24].view(dv.FAULT_DTYPE),
+                   device.read_arenas(ctx, dw), dw.pool.cpu().numpy())
+            assert compare(f"capture, pass {k}", got, exp) == []
+    finally:
+        ctx.close()
