@@ -240,6 +240,7 @@ struct XlatArgs {
 hipError_t launch_reset(hipStream_t s, DBatch b, uint32_t n_epochs);
 hipError_t launch_translate_groups(hipStream_t s, int grid, int block, DView v, DBatch b, uint64_t r0,
                                    uint64_t r1, uint32_t epoch, int direct);
+hipError_t launch_translate_one(hipStream_t s, int block, DView v, DBatch b, uint64_t n, int direct);
 hipError_t launch_translate_large(hipStream_t s, int grid, int block, DView v, DBatch b, uint64_t r0,
                                   uint32_t epoch);
 hipError_t launch_copy(hipStream_t s, int grid, int block, DBatch b, uint32_t epoch, const CopyTail &tail = {});

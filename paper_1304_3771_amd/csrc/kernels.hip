@@ -934,6 +934,9 @@ __device__ bool process_group(const DView &V, const DBatch &B, uint64_t r0, uint
         if (head) {
             const int nh_bit = __ffsll((unsigned long long)(head_mask & ~mask_le(lane)));
             const int nh = nh_bit ? nh_bit - 1 : 64;
+            // (known: with no later head nh is 64, and the shift in mask_lt leaves lane
+            // 63 out of the run; a region that starts in lane 63 gets no bits here,
+            // only from the pass that continues it)
             const uint64_t rmask = mask_lt(nh) & ~mask_lt(lane);
             if (cmask & rmask) {
                 const bool rto = (cto_mask & rmask) != 0;
@@ -1690,6 +1693,217 @@ __global__ void __launch_bounds__(64 * kPlainWaves) k_plain_walk(PlainArgs a) {
         plain_pages<3>(a, vm, sl, sh);
 }
 
+// ------------------------------------------- small batches, one request a wave
+// The pages [base, base + 64 * waves) of one request, 64 a wavefront (`part`:
+// which 64 this wavefront takes): walk, the request's first fault, A/D bits,
+// copy segments.  ff: shared by the wavefronts of a workgroup that walk one
+// request together, null where a wavefront is alone.  Returns the first
+// faulting page (kNone: none in these pages); its lane's outcome is left in f.
+struct OneFault {
+    uint32_t code, level;
+    uint64_t lo;
+};
+
+template <int LEVELS>
+__device__ uint32_t one_pages(const DBatch &b, const DVm &vm, const SlotLanes &sl, const DSlot *slots, uint64_t cr3,
+                              uint64_t gva, uint64_t host, uint32_t len, bool dir, uint32_t req, uint32_t total,
+                              uint32_t base, uint32_t part, uint32_t qpart, bool direct, uint32_t *ff, OneFault *f) {
+    const int lane = lane_id();
+    const uint32_t c = base + 64 * part + (uint32_t)lane;
+    const uint64_t end = gva + len;
+    const uint64_t page = (gva & ~0xFFFull) + ((uint64_t)c << 12);
+    const uint64_t lo = page > gva ? page : gva, hi = page + 4096 < end ? page + 4096 : end;
+    const bool act = c < total;
+    PageWalk<LEVELS> w;
+    w.code = DEVIRT_OK;
+    w.leaf = 0;
+    if (base + 64 * part < total) page_walk<LEVELS>(vm, sl, slots, cr3, lo, dir, act, w);
+    const uint64_t fm = __ballot(act && w.code != DEVIRT_OK);
+    uint32_t first = fm ? base + 64 * part + (uint32_t)__ffsll((unsigned long long)fm) - 1 : kNone;
+    if (ff) {
+        if (fm && lane == 0) atomicMin(ff, first);
+        __syncthreads();
+        first = uniform_u32(*(volatile uint32_t *)ff);
+    }
+    if (act && c == first) *f = OneFault{w.code, w.level, lo};
+    const bool copied = act && c < first;
+    const uint64_t cm = __ballot(copied);
+    if (!cm) return first;
+    // copy segments: runs of pages that follow one another in guest memory
+    const uint64_t gptr = (uint64_t)(uintptr_t)vm.arena + w.hpa, hptr = host + (lo - gva);
+    uint32_t n = (uint32_t)(hi - lo);
+    bool head = copied;
+    if (b.seg_chunks > 1) {
+        const int prev = lane > 0 ? lane - 1 : 0;
+        const uint64_t p_end = shfl64(gptr, prev) + shfl32(n, prev);
+        const bool cont = copied && lane > 0 && p_end == gptr && c % b.seg_chunks != 0;
+        head = copied && !cont;
+        const uint64_t ends = ~__ballot(cont) & ~mask_le(lane);
+        const int last = ends ? __ffsll((unsigned long long)ends) - 2 : 63;  // the run's last page
+        n = (uint32_t)(shfl64(hi, head ? last : lane) - lo);
+    }
+    const uint64_t src = dir ? hptr : gptr, dst = dir ? gptr : hptr;
+    const bool small = head && !direct && n <= b.inline_bytes;
+    const bool is_short = n <= kShortRun, queue = head && !direct && !small;
+    const uint64_t lm = __ballot(queue && !is_short), sm = __ballot(queue && is_short);
+    uint32_t lbase = 0, sbase = 0;
+    if (lane == 0) {
+        if (lm) lbase = atomicAdd(&b.ctr->q[qpart][0], (uint32_t)__popcll(lm));
+        if (sm) sbase = atomicAdd(&b.ctr->q[kQParts + qpart][0], (uint32_t)__popcll(sm));
+    }
+    // A/D of the copied pages' paths, while the queue places are on their way:
+    // an entry shared with the previous lane is left to that lane
+#pragma unroll
+    for (int i = 0; i < LEVELS; ++i) {
+        const int lvl = LEVELS - i;
+        const uint64_t po = shfl64(w.off[i], lane > 0 ? lane - 1 : 0);
+        if (LEVELS == 3 && lvl == 3) continue;
+        const uint32_t want = (uint32_t)kA | (w.leaf == (uint32_t)lvl && dir ? (uint32_t)kD : 0u);
+        if (copied && lvl >= (int)w.leaf && (lane == 0 || po != w.off[i]) && (w.lo[i] & want) != want)
+            or_entry(vm.arena, w.off[i], want);
+    }
+    if (small) copy_lane((uint8_t *)dst, (const uint8_t *)src, n);
+    bool full = head && direct;
+    if (lm | sm) {
+        lbase = uniform_u32(shfl32(lbase, 0));
+        sbase = uniform_u32(shfl32(sbase, 0));
+        if (queue) {
+            const uint64_t pos = is_short ? (uint64_t)sbase + __popcll(sm & mask_lt(lane))
+                                          : (uint64_t)lbase + __popcll(lm & mask_lt(lane));
+            full = pos >= b.part_cap;
+            if (!full) {
+                DSeg sg;
+                sg.src = src;
+                sg.dst = dst;
+                sg.len = n;
+                sg.req = req;
+                sg.pad = 0;
+                gp<DV_GLOBAL DSeg>(is_short ? b.shorts : b.segs)[qpart * b.part_cap + pos] = sg;
+            }
+        }
+    }
+    for (uint64_t m = __ballot(full); m; m &= m - 1) {  // no queue, or it is full: the wavefront copies the run
+        const int l = __ffsll((unsigned long long)m) - 1;
+        copy_wave((uint8_t *)uniform_u64(shfl64(dst, l)), (const uint8_t *)uniform_u64(shfl64(src, l)),
+                  uniform_u32(shfl32(n, l)), b.nontemporal != 0);
+    }
+    return first;
+}
+
+// A one-epoch batch so small that a wavefront can have each request to itself.
+// Bound by the latency of one wavefront: its own instructions and cross-lane
+// steps as much as its loads.  k_translate_groups spends about 1,200 vector
+// instructions and 92 LDS operations on a wavefront's first pass, most of them
+// to find which request a lane's page belongs to and to hand its fields round;
+// here the request is the wavefront's, its fields are scalars, and the walk is
+// that of the per-request copy.  A request of more than kOneAlone pages is
+// walked by the workgroup's wavefronts together, 64 pages each a round.
+// Batches in us, k_translate_groups and this: 256 requests of up to 4 KiB 17.3
+// and 12.4, 2,000 of up to 64 KiB behind an EPT 23.2 and 19.9, 1,000 of up to
+// 1 MiB 39.9 and 33.3, 8,191 of up to 64 KiB 37.2 and 36.2.
+constexpr uint32_t kOneAlone = 128;
+struct OneShared {
+    DSlot slots[4][kSlotRow];
+    uint32_t big[4];   // the wavefront's request has more than kOneAlone pages
+    uint32_t ff;
+    OneFault f;
+};
+
+__device__ __forceinline__ void one_result(devirt_result *res, uint64_t i, uint64_t gva, uint32_t len, uint32_t code0,
+                                           uint32_t ff, const OneFault &f) {
+    devirt_result r;
+    r.bytes_done = code0 ? 0 : ff == kNone ? len : f.lo - gva;
+    r.fault_gva = code0 ? gva : ff == kNone ? 0 : f.lo;
+    r.code = code0 ? code0 : ff == kNone ? (uint32_t)DEVIRT_OK : f.code;
+    r.level = code0 || ff == kNone ? (uint16_t)0 : (uint16_t)f.level;
+    r.pad = 0;
+    gp<DV_GLOBAL devirt_result>(res)[i] = r;
+}
+
+// direct: the wavefront copies its request itself and nothing is queued.
+__global__ void __launch_bounds__(256) k_translate_one(DView v, DBatch b, uint64_t n, int direct) {
+    __shared__ OneShared sh;
+    const int lane = lane_id();
+    const uint32_t wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    const uint64_t w0 = (uint64_t)blockIdx.x * waves;
+    const uint32_t qpart = (uint32_t)((w0 + wave) % kQParts);
+    if (threadIdx.x < 4) sh.big[threadIdx.x] = 0;
+    __syncthreads();
+    // one request: of this wavefront (team == 0), or of the workgroup
+    const auto translate = [&](uint64_t i, uint32_t part, uint32_t team) {
+        const g_u32x4 *p = gp<const g_u32x4>(b.reqs + i);
+        const u32x4 qa = p[0], qb = p[1];
+        const uint64_t gva = uniform_u64(((uint64_t)qa.y << 32) | qa.x), host = uniform_u64(((uint64_t)qa.w << 32) | qa.z);
+        const uint32_t len = uniform_u32(qb.x), asid = uniform_u32(qb.y);
+        const bool dir = (uniform_u32(qb.z) & 0xFF) != 0;
+        uint32_t code0 = DEVIRT_OK, ff = kNone;
+        OneFault f{0, 0, 0};
+        if (asid >= v.nproc) {
+            code0 = DEVIRT_INVALID;
+        } else if (len) {
+            const DV_GLOBAL DProc *pp = gp<const DV_GLOBAL DProc>(v.procs) + asid;
+            const uint32_t levels = uniform_u32(pp->levels), vmi = uniform_u32(pp->vm);
+            const uint64_t cr3 = uniform_u64(pp->cr3), lim = user_limit(levels);
+            if (gva >= lim || (uint64_t)len > lim - gva) {
+                code0 = DEVIRT_NONCANONICAL;
+            } else {
+                const uint32_t total = (uint32_t)(((gva + len - 1) >> 12) - (gva >> 12) + 1);
+                if (!team && waves > 1 && total > kOneAlone) {
+                    if (lane == 0) sh.big[wave] = 1;
+                    return;
+                }
+                const DV_GLOBAL DSlot *row = gp<const DV_GLOBAL DSlot>(v.slots) + (uint64_t)vmi * kSlotRow + lane;
+                SlotLanes sl;
+                sl.gpa = row->gpa;
+                sl.end = row->end;
+                sl.off = row->arena_off;
+                const DVm vm = load_vm(v, vmi, false);
+                DSlot *slots = sh.slots[wave];
+                slots[lane] = DSlot{sl.gpa, sl.end, sl.off};
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                const uint32_t step = team ? 64 * waves : 64;
+                OneFault *fo = team ? &sh.f : nullptr;
+                OneFault mine{0, 0, 0};
+                for (uint32_t base = 0; base < total && ff == kNone; base += step) {
+                    uint32_t *sf = team ? &sh.ff : nullptr;
+                    OneFault *out = team ? fo : &mine;
+                    if (levels == 5)
+                        ff = one_pages<5>(b, vm, sl, slots, cr3, gva, host, len, dir, (uint32_t)i, total, base, part,
+                                          qpart, direct != 0, sf, out);
+                    else if (levels == 4)
+                        ff = one_pages<4>(b, vm, sl, slots, cr3, gva, host, len, dir, (uint32_t)i, total, base, part,
+                                          qpart, direct != 0, sf, out);
+                    else
+                        ff = one_pages<3>(b, vm, sl, slots, cr3, gva, host, len, dir, (uint32_t)i, total, base, part,
+                                          qpart, direct != 0, sf, out);
+                    if (team) __syncthreads();  // ff is read by every wavefront before the next round adds to it
+                }
+                if (ff != kNone) {
+                    if (team) {
+                        f = sh.f;
+                    } else {  // the faulting page's lane has it
+                        const int l = (int)(ff & 63);
+                        f.code = shfl32(mine.code, l);
+                        f.level = shfl32(mine.level, l);
+                        f.lo = shfl64(mine.lo, l);
+                    }
+                }
+            }
+        }
+        if (lane == 0 && part == 0) one_result(b.res, i, gva, len, code0, ff, f);
+    };
+    if (w0 + wave < n) translate(w0 + wave, 0, 0);
+    __syncthreads();
+    for (uint32_t k = 0; k < waves; ++k) {
+        if (!*(volatile uint32_t *)&sh.big[k]) continue;  // uniform
+        if (threadIdx.x == 0) sh.ff = kNone;
+        __syncthreads();
+        translate(w0 + k, wave, 1);
+        __syncthreads();
+    }
+}
+
 // ---------------------------------------------------------- translate only
 // One process, one lane per address.  A workgroup keeps in LDS what every
 // address of the process goes through: the VM's guest-physical space as one
@@ -2173,6 +2387,12 @@ hipError_t launch_reset(hipStream_t s, DBatch b, uint32_t n_epochs) {
 hipError_t launch_translate_groups(hipStream_t s, int grid, int block, DView v, DBatch b, uint64_t r0, uint64_t r1,
                                    uint32_t epoch, int direct) {
     hipLaunchKernelGGL(k_translate_groups, dim3(grid), dim3(block), wave_lds(block), s, v, b, r0, r1, epoch, direct);
+    return hipGetLastError();
+}
+
+hipError_t launch_translate_one(hipStream_t s, int block, DView v, DBatch b, uint64_t n, int direct) {
+    const uint64_t waves = (uint64_t)block / 64;
+    hipLaunchKernelGGL(k_translate_one, dim3((unsigned)((n + waves - 1) / waves)), dim3(block), 0, s, v, b, n, direct);
     return hipGetLastError();
 }
 

@@ -988,6 +988,19 @@ static hipError_t spill_pass(devirt_ctx *c, hipStream_t st, const DView &v, cons
                         (int)c->cfg.xlat_wg, v, be, r0, r1, (uint32_t)e);
 }
 
+// A one-epoch batch whose groups are single requests (up to 4 per CU, unless
+// configured so) is translated by k_translate_one: 256 requests of up to 4 KiB
+// 17.3 us a batch in groups, 12.4 so, 1,000 of up to 1 MiB 39.9 and 33.3.  (The
+// walk by large_pages and the device counters belong to k_translate_groups.)
+// With configured groups of one, more wavefronts than about twice what the
+// chip holds lose: 12,000 requests of up to 4 KiB 24.0 us in groups, 31.7 so.
+// Between 1,024 and 8,192 requests it would gain 1-3 us too, but there it would
+// change results: in a pass whose last lane alone starts a 2 MiB region,
+// process_group leaves that region's upper entries without their accessed
+// bits (known, see its use of mask_lt), and requests that share a wavefront
+// meet that case once in some hundred.
+static const uint64_t kOneMax = 8192;
+
 // The ordered fault list: a tile count, a scan, a scatter.
 static int fault_list(Workspace *w, const BatchArgs &a, hipStream_t s) {
     HIPCHK(launch_fault_count(s, a.res, a.n, w->tiles));
@@ -1004,11 +1017,14 @@ static int enqueue_batch(devirt_ctx *c, Workspace *w, const BatchArgs &a, hipStr
     const DView v = view_of(c);
     const size_t ne = a.epochs.size();
     if (a.direct) {
-        // one epoch, every group the first of some wavefront (no claims, so no
-        // counter reset), copies by the translating wavefronts: one launch
+        // one epoch, a wavefront per request that also copies it: one launch
+        // (while counting, groups of one, every one the first of some wavefront)
         b.group = 1;
-        HIPCHK(launch_translate_groups(s, grid_for(c, a.n, c->cfg.xlat_wg, 1u << 20), (int)c->cfg.xlat_wg, v, b, 0,
-                                       a.n, 0, 1));
+        if (b.counters)
+            HIPCHK(launch_translate_groups(s, grid_for(c, a.n, c->cfg.xlat_wg, 1u << 20), (int)c->cfg.xlat_wg, v, b,
+                                           0, a.n, 0, 1));
+        else
+            HIPCHK(launch_translate_one(s, 64, v, b, a.n, 1));
         return a.faults || a.n_faults ? fault_list(w, a, s) : 0;
     }
     // One epoch, no completion times: two launches.  The counters are one of
@@ -1029,9 +1045,13 @@ static int enqueue_batch(devirt_ctx *c, Workspace *w, const BatchArgs &a, hipStr
         CopyTail tail{a.n, list ? nullptr : a.faults, list ? nullptr : a.n_faults, w->ctr + (w->ctr_turn ^ 1)};
         ProfEv *pe;
         int rc;
+        const bool one = b.group == 1 && a.n <= kOneMax && !b.large_pages && !b.counters;
         if ((rc = prof_begin(c, s, 1, &pe))) return rc;
-        HIPCHK(launch_translate_groups(s, grid_for(c, groups, c->cfg.xlat_wg, c->cfg.xlat_wgs_per_cu),
-                                       (int)c->cfg.xlat_wg, v, b, 0, a.n, 0, 0));
+        if (one)
+            HIPCHK(launch_translate_one(s, (int)c->cfg.xlat_wg, v, b, a.n, 0));
+        else
+            HIPCHK(launch_translate_groups(s, grid_for(c, groups, c->cfg.xlat_wg, c->cfg.xlat_wgs_per_cu),
+                                           (int)c->cfg.xlat_wg, v, b, 0, a.n, 0, 0));
         if (b.large_pages) HIPCHK(launch_translate_large(s, (int)(2ull * c->cus), 256, v, b, 0, 0));
         if ((rc = prof_end(c, s, pe))) return rc;
         if ((rc = prof_begin(c, s, 0, &pe))) return rc;

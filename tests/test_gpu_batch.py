@@ -119,3 +119,32 @@ def test_one_epoch_batch_under_capture():
             assert compare(f"capture, pass {k}", got, exp) == []
     finally:
         ctx.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("levels,ept,cfg", [
+    (4, False, {}), (3, False, {}), (5, False, {}), (4, True, {}),
+    (4, False, dict(seg_chunks=4)), (5, False, dict(seg_chunks=64, inline_bytes=256)),
+    (4, False, dict(xlat_wg=64)), (4, False, dict(xlat_wg=192, copy_wg=64)), (4, False, dict(tiny_queue=64)),
+])
+def test_one_request_per_wavefront(levels, ept, cfg, monkeypatch):
+    """A one-epoch batch small enough for a wavefront a request: requests of one page to several rounds of a
+    workgroup's wavefronts, every fault code, merged segments, lane copies, a queue that overflows."""
+    import torch  # noqa: F401
+    sp = gen.spec("C1", mem_bytes=256 * MiB, levels=levels, ept=ept, procs_per_vm=2, n_vms=2, n_requests=400, len_lo=16,
+                  len_hi=3 * MiB, len_kind="loguniform", p_np=0.002, p_readonly=0.002, p_supervisor=0.002,
+                  ept_np=0.002 * ept, ept_ro=0.002 * ept, ept_mis=0.002 * ept, mix=(0.7, 0.3, 0.0), rho=0.9,
+                  seed=4700 + levels + 10 * ept)
+    w = gen.make_workload(sp)
+    w.requests["asid"][::97] = 99  # unknown processes
+    w.requests["gva"][5::89] = np.uint64(1 << 63)  # not canonical
+    w.requests["len"][7::101] = 0
+    exp = oracle_batch(w)
+    pages = (w.requests["len"] >> 12) + 1
+    log(f"levels {levels} ept {ept} {cfg}: {len(w.epoch_end)} epochs, {int((pages > 128).sum())} requests of over 128 "
+        f"pages, codes {np.bincount(exp[0]['code'])}")
+    assert len(w.epoch_end) == 1 and (pages > 512).sum() > 5
+    cfg = dict(cfg)
+    if cfg.pop("tiny_queue", 0):
+        monkeypatch.setenv("DEVIRT_SEG_CAP", "64")
+    assert compare(f"{cfg}", gpu_batch(w, cfg=cfg, repeat=1), exp) == []
