@@ -179,22 +179,38 @@ def _ptr(x):
     raise TypeError(f"cannot take a pointer of {type(x)}")
 
 
+def _torch_stream():
+    """The handle of torch's current stream on its current device (None without a GPU).
+
+    The first call with a GPU puts the raw lookup in this function's place: building a Stream object and asking
+    whether there is a GPU took 3.5 us of the 7.3 us a small call spends on the host."""
+    global _current_stream
+    try:
+        import torch
+        if not torch.cuda.is_available():
+            return None
+        handle = torch.cuda.current_stream().cuda_stream  # initialises torch's side
+    except Exception:  # pragma: no cover
+        return None
+    device, raw = getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if device is not None and raw is not None:
+        _current_stream = lambda: raw(device())  # noqa: E731
+    return handle
+
+
+_current_stream = _torch_stream
+
+
 def _stream(s):
     if s is None:
-        try:
-            import torch
-            if torch.cuda.is_available():
-                return torch.cuda.current_stream().cuda_stream
-        except Exception:  # pragma: no cover
-            pass
-        return None
+        return _current_stream()
     if isinstance(s, int):
         return s
     return s.cuda_stream
 
 
 def _check(fn: str, rc: int):
-    if rc != 0:
+    if rc:
         msg = lib().devirt_last_error()
         raise DevirtError(fn, rc, msg.decode() if msg else "")
 
