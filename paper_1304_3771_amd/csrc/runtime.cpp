@@ -995,10 +995,7 @@ static hipError_t spill_pass(devirt_ctx *c, hipStream_t st, const DView &v, cons
 // With configured groups of one, more wavefronts than about twice what the
 // chip holds lose: 12,000 requests of up to 4 KiB 24.0 us in groups, 31.7 so.
 // Between 1,024 and 8,192 requests it would gain 1-3 us too, but there it would
-// change results: in a pass whose last lane alone starts a 2 MiB region,
-// process_group leaves that region's upper entries without their accessed
-// bits (known, see its use of mask_lt), and requests that share a wavefront
-// meet that case once in some hundred.
+// change which accessed bits a batch leaves unset (see last_head_lost).
 static const uint64_t kOneMax = 8192;
 
 // The ordered fault list: a tile count, a scan, a scatter.
