@@ -267,8 +267,11 @@ struct MapArgs {
     devirt_result *res;
     uint64_t *n_used;
     uint64_t n_pool;
-    const uint64_t *pool_gpa;             // device, n_pool
-    uint64_t *pool_hpa;                   // device, n_pool: from the host, or (ept_pool) from k_map_pool
+    // the first m pool frames, the most the batch can use: staged in host memory
+    // (gpa, then hpa), from which the kernels fetch them into the two arrays
+    const uint64_t *staged;
+    const uint64_t *pool_gpa;             // device, m; pool_hpa follows it
+    uint64_t *pool_hpa;                   // device, m: from the host, or (ept_pool) from k_map_pool
     int ept_pool;                         // the VM has an EPT: pool frames are translated on the device
     // EPT maps (devirt_ept_map_pages): the maps name guest-physical pages of
     // VM `vm` and the arena pages behind them, and the writes go to its EPT;
@@ -285,7 +288,7 @@ struct MapArgs {
     // pages: a hash set of (page << kMapIdxBits | highest map index), ~0 when empty
     uint64_t *pset;
     uint32_t pset_log2;
-    uint64_t *sc;                         // 4 scalars
+    uint64_t *sc;                         // 4 scalars: distinct keys, pages do not ascend, -, failed
 };
 hipError_t launch_map(hipStream_t s, const MapArgs &a);
 

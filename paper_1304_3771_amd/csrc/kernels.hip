@@ -2674,84 +2674,125 @@ __device__ void page_note(const MapArgs &a, uint64_t page, uint64_t i) {
     }
 }
 
-// Fill `ones` with ~0 (empty set slots, list padding) and `zeros` with 0.
-__global__ void __launch_bounds__(256) k_map_clear(uint64_t *ones, uint64_t n_ones, uint64_t *zeros, uint64_t n_zeros) {
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n_ones + n_zeros; t += stride) {
-        if (t < n_ones)
-            ones[t] = ~0ull;
-        else
-            zeros[t - n_ones] = 0;
-    }
+// Fill `ones` with ~0 (empty set slots, list padding) and `zeros` with 0, and
+// fetch the pool from the host memory it is staged in: only the frames that
+// the batch can use, and without a copy operation of their own (with one, and
+// the wait for the one before, 16 maps took 42 us a call; now 20).
+__global__ void __launch_bounds__(256) k_map_clear(uint64_t *ones, uint64_t n_ones, uint64_t *zeros, uint64_t n_zeros,
+                                                   const uint64_t *staged, uint64_t *pool, uint64_t n_pool) {
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x, t0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (uint64_t t = t0; t < n_pool; t += stride) pool[t] = staged[t];
+    for (uint64_t t = t0; t < n_ones / 2; t += stride) gp<g_u32x4>(ones)[t] = (u32x4){~0u, ~0u, ~0u, ~0u};
+    if (t0 == 0 && (n_ones & 1)) ones[n_ones - 1] = ~0ull;
+    if (t0 < n_zeros) zeros[t0] = 0;
 }
 
-// One lane per map: its result; the tables its path lacks go into the set
-// (a key the previous lane of the wavefront holds in the same position is
-// left to that lane); a successful map is noted for its page.
+// Whether map m is one that is walked (its addresses and flags are valid).
+__device__ __forceinline__ bool map_valid(const MapArgs &a, const DVm &vm, uint32_t levels, const devirt_map &m) {
+    if (a.ept_map) {  // gva: the guest-physical page; gpa: the arena page behind it
+        const uint32_t perms = m.flags & 7u;
+        return !((m.gva & 0xFFFull) || (m.gva >> 48) || (m.gpa & 0xFFFull) || m.gpa >= vm.arena_bytes ||
+                 vm.arena_bytes - m.gpa < 4096 || (m.flags & ~7u) || perms == 0 || (perms & 3u) == 2u);
+    }
+    return !((m.gva & 0xFFFull) || m.gva >= user_limit(levels) || (m.gpa & 0xFFFull) || m.gpa >= (1ull << 52));
+}
+
+// A map's result, and the keys of the tables its path lacks (k, from the top
+// level down, ~0 after the last).
+__device__ __forceinline__ bool map_one(const MapArgs &a, const DVm &vm, const DProc &p, const devirt_map &m,
+                                        devirt_result &r, uint64_t (&k)[4]) {
+    r.bytes_done = 0;
+    r.fault_gva = m.gva;
+    r.code = DEVIRT_NONCANONICAL;
+    r.level = 0;
+    r.pad = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) k[j] = ~0ull;
+    if (!map_valid(a, vm, p.levels, m)) return false;
+    uint32_t level = 0, missing = 0;
+    r.code = a.ept_map ? ept_map_walk(vm, m.gva, level, missing) : map_walk(vm, p, m.gva, level, missing);
+    r.level = (uint16_t)level;
+    if (r.code != DEVIRT_OK) return false;
+    r.bytes_done = 4096;
+    r.fault_gva = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j)
+        if (missing > j + 1) k[j] = map_key(missing - 1 - j, m.gva);
+    return true;
+}
+
+// One lane per map: its result; the tables its path lacks go into the set, a
+// key that the map before it adds left to that map (a valid map that shares a
+// lacking table with this one lacks all of the tables below the same entry).
+// Maps whose pages do not ascend set sc[1]: only then can two name one page.
+//
+// Bound by device atomics.  On one address they take turns, 13 ns each, so a
+// region's upper tables must not be added by every wavefront; and a page set
+// costs an atomic per map, so maps in ascending order, which is how a region
+// is mapped, do without one (and the others note their pages in the next
+// launch).  131,072 maps of a fresh region: this launch 38.8 -> 10.1 us, the
+// call 85.9 -> 38.5; 131,072 scattered remaps 51.5 -> 36.7 a call.
 __global__ void __launch_bounds__(256) k_map_walk(MapArgs a) {
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int lane = lane_id();
     const bool live = i < a.n;
+    const bool known = a.ept_map || a.asid < a.v.nproc;
+    DProc p = {0, 0, 4};
+    DVm vm = {};
+    if (known) {
+        if (!a.ept_map) p = a.v.procs[a.asid];
+        vm = a.v.vms[a.ept_map ? a.vm : p.vm];
+    }
     uint64_t k[4] = {~0ull, ~0ull, ~0ull, ~0ull};
-    uint64_t gva = 0;
-    bool ok = false;
+    devirt_map m = {0, 0, 0, 0};
     if (live) {
-        const devirt_map m = a.maps[i];
-        gva = m.gva;
+        m = a.maps[i];
         devirt_result r;
-        r.bytes_done = 0;
-        r.fault_gva = m.gva;
-        r.code = DEVIRT_OK;
-        r.level = 0;
-        r.pad = 0;
-        if (a.ept_map) {  // gva: the guest-physical page; gpa: the arena page behind it
-            const DVm vm = a.v.vms[a.vm];
-            const uint32_t perms = m.flags & 7u;
-            if ((m.gva & 0xFFFull) || (m.gva >> 48) || (m.gpa & 0xFFFull) || m.gpa >= vm.arena_bytes ||
-                vm.arena_bytes - m.gpa < 4096 || (m.flags & ~7u) || perms == 0 || (perms & 3u) == 2u) {
-                r.code = DEVIRT_NONCANONICAL;
-            } else {
-                uint32_t level = 0, missing = 0;
-                r.code = ept_map_walk(vm, m.gva, level, missing);
-                r.level = (uint16_t)level;
-                if (r.code == DEVIRT_OK) {
-                    r.bytes_done = 4096;
-                    r.fault_gva = 0;
-                    ok = true;
-                    int j = 0;
-                    for (uint32_t l = missing ? missing - 1 : 0; l >= 1 && j < 4; --l) k[j++] = map_key(l, m.gva);
-                }
-            }
-        } else if (a.asid >= a.v.nproc) {
-            r.code = DEVIRT_INVALID;
+        if (known) {
+            map_one(a, vm, p, m, r, k);
         } else {
-            const DProc p = a.v.procs[a.asid];
-            const DVm vm = a.v.vms[p.vm];
-            if ((m.gva & 0xFFFull) || m.gva >= user_limit(p.levels) || (m.gpa & 0xFFFull) || m.gpa >= (1ull << 52)) {
-                r.code = DEVIRT_NONCANONICAL;
-            } else {
-                uint32_t level = 0, missing = 0;
-                r.code = map_walk(vm, p, m.gva, level, missing);
-                r.level = (uint16_t)level;
-                if (r.code == DEVIRT_OK) {
-                    r.bytes_done = 4096;
-                    r.fault_gva = 0;
-                    ok = true;
-                    int j = 0;
-                    for (uint32_t l = missing ? missing - 1 : 0; l >= 1 && j < 4; --l) k[j++] = map_key(l, m.gva);
-                }
-            }
+            r = devirt_result{0, m.gva, DEVIRT_INVALID, 0, 0};
         }
         a.res[i] = r;
     }
-    const int lane = lane_id();
+    // the map before, and whether it adds keys
+    devirt_map q = {0, 0, 0, 0};
+    q.gva = shfl64(m.gva, lane > 0 ? lane - 1 : 0);
+    bool before = shfl32(live && known && map_valid(a, vm, p.levels, m) ? 1u : 0u, lane > 0 ? lane - 1 : 0) != 0;
+    if (lane == 0 && live && i > 0) {
+        q = a.maps[i - 1];
+        before = known && map_valid(a, vm, p.levels, q);
+    }
+    if (i == 0) before = false;
+    const bool descends = live && i > 0 && (q.gva >> 12) >= (m.gva >> 12);
+    // by many wavefronts, the same value: an ordinary store, which stays in the
+    // cache (an atomic or volatile one took turns on the line, 30 ns each)
+    if (__ballot(descends) && lane == 0) gp<g_u64>(a.sc)[1] = 1;
     bool want[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const uint64_t prev = shfl64(k[j], lane > 0 ? lane - 1 : 0);
-        want[j] = k[j] != ~0ull && (lane == 0 || prev != k[j]);
+        const uint32_t l = 8u - (uint32_t)(k[j] >> 56);  // the key's level
+        want[j] = k[j] != ~0ull && !(before && map_key(l, q.gva) == k[j]);
     }
     tset_insert4(a, k, want);
-    if (ok) page_note(a, gva >> 12, i);
+}
+
+// The page set, when the maps' pages do not ascend: each successful map is
+// noted for its page.
+__device__ __forceinline__ void note_pages(const MapArgs &a) {
+    if (a.sc[1] == 0) return;
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.n; i += stride)
+        if (a.res[i].code == DEVIRT_OK) page_note(a, a.maps[i].gva >> 12, i);
+}
+
+// Whether successful map t is the last of its page.
+__device__ __forceinline__ bool last_of_page(const MapArgs &a, uint64_t page, uint64_t t) {
+    if (a.sc[1] == 0) return true;
+    const uint64_t mask = (1ull << a.pset_log2) - 1;
+    uint64_t h = hash_slot(page, a.pset_log2);
+    for (uint64_t probe = 0; probe <= mask && (a.pset[h] >> kMapIdxBits) != page; ++probe) h = (h + 1) & mask;
+    return a.pset[h] == ((page << kMapIdxBits) | t);
 }
 
 // A VM with an EPT: the pool frames the batch takes (the first sc[0]) are
@@ -2792,6 +2833,7 @@ __device__ __forceinline__ bool pool_short(const MapArgs &a) { return a.sc[3] !=
 // launch zeroes the new tables, 16 bytes per lane.
 __global__ void __launch_bounds__(256) k_map_rank_zero(const MapArgs a) {
     __shared__ uint64_t tile[256];
+    note_pages(a);
     const uint64_t nt = new_tables(a);
     const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     DVm zvm;
@@ -2881,6 +2923,7 @@ __global__ void __launch_bounds__(256) k_map_merge(const MapArgs a, const uint64
 
 // Zero the new tables (after a long list's sort).
 __global__ void __launch_bounds__(256) k_map_zero(const MapArgs a) {
+    note_pages(a);
     const uint64_t nt = new_tables(a);
     DVm zvm;
     if (!nt || !map_vm(a, zvm)) return;
@@ -2920,11 +2963,7 @@ __global__ void __launch_bounds__(256) k_map_write(const MapArgs a) {
             a.res[t].fault_gva = m.gva;
             return;
         }
-        const uint64_t page = m.gva >> 12;
-        const uint64_t mask = (1ull << a.pset_log2) - 1;
-        uint64_t h = hash_slot(page, a.pset_log2);
-        for (uint64_t probe = 0; probe <= mask && (a.pset[h] >> kMapIdxBits) != page; ++probe) h = (h + 1) & mask;
-        if (a.pset[h] != ((page << kMapIdxBits) | t)) return;  // not the page's last map
+        if (!last_of_page(a, m.gva >> 12, t)) return;
         const int64_t j = find_key(uniq, nt, map_key(1, m.gva));
         const uint64_t pt = j >= 0 ? a.pool_hpa[j] : existing_ept_table(vm, m.gva, 1);
         store_entry(vm.arena, ept_slot(pt, 1, m.gva), m.gpa | (m.flags & 7u) | kEptWb);
@@ -2960,11 +2999,7 @@ __global__ void __launch_bounds__(256) k_map_write(const MapArgs a) {
         a.res[t].fault_gva = m.gva;
         return;
     }
-    const uint64_t page = m.gva >> 12;
-    const uint64_t mask = (1ull << a.pset_log2) - 1;
-    uint64_t h = hash_slot(page, a.pset_log2);
-    for (uint64_t probe = 0; probe <= mask && (a.pset[h] >> kMapIdxBits) != page; ++probe) h = (h + 1) & mask;
-    if (a.pset[h] != ((page << kMapIdxBits) | t)) return;  // not the page's last map
+    if (!last_of_page(a, m.gva >> 12, t)) return;
     const int64_t j = find_key(uniq, nt, map_key(1, m.gva));
     uint64_t pt = 0;
     if (j >= 0)
@@ -2981,14 +3016,15 @@ hipError_t launch_map(hipStream_t s, const MapArgs &a) {
     const uint64_t nset = (1ull << a.tset_log2), npset = (1ull << a.pset_log2);
     // tset, tkeys and pset are contiguous, then sc
     const uint64_t ones = nset + a.m + npset, zeros = 4;
-    hipLaunchKernelGGL(k_map_clear, dim3(blocks_for(std::min<uint64_t>(ones + zeros, 1ull << 22))), dim3(256), 0, s,
-                       a.tset, ones, a.sc, zeros);
+    hipLaunchKernelGGL(k_map_clear, dim3(blocks_for(std::min<uint64_t>(std::max(ones / 2, 2 * a.m), 1ull << 18))),
+                       dim3(256), 0, s, a.tset, ones, a.sc, zeros, a.staged, (uint64_t *)a.pool_gpa, 2 * a.m);
     hipLaunchKernelGGL(k_map_walk, dim3(blocks_for(a.n)), dim3(256), 0, s, a);
     if (a.ept_pool) hipLaunchKernelGGL(k_map_pool, dim3(blocks_for(a.m)), dim3(256), 0, s, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (a.rank) {
-        // enough lanes to zero every possible new table in one sweep (at most 2^22)
-        hipLaunchKernelGGL(k_map_rank_zero, dim3(blocks_for(std::max(a.m, std::min<uint64_t>(a.m * 256, 1ull << 22)))),
+        // lanes to zero the new tables 16 bytes each, at most 2^18 (four
+        // workgroups a CU: a workgroup without a table still has to be launched)
+        hipLaunchKernelGGL(k_map_rank_zero, dim3(blocks_for(std::max(a.m, std::min<uint64_t>(a.m * 256, 1ull << 18)))),
                            dim3(256), 0, s, a);
     } else {
         // merge rounds for m keys; the tile sort's output buffer is chosen so

@@ -98,12 +98,12 @@ Workspace::~Workspace() {
     hipFree(t0);
     hipFree(spill);
     hipFree(large);
-    if (map_ev) {
-        hipEventSynchronize(map_ev);
-        hipEventDestroy(map_ev);
-    }
+    if (map_pool_host) hipDeviceSynchronize();  // kernels read the staged pools
+    for (hipEvent_t e : map_ev)
+        if (e) hipEventDestroy(e);
     hipFree(map_buf);
     hipHostFree(map_pool_host);
+    for (uint64_t *p : map_pool_old) hipHostFree(p);
 }
 
 // While a serving loop runs, only its own thread may drive the context.
@@ -680,8 +680,41 @@ int dv_map_pool_check(const devirt_ctx *c, uint32_t asid, const uint64_t *pool_g
     return 0;
 }
 
+// Room for `words` in the half of the pinned pool staging in use.  A half that
+// cannot take them is left with an event behind its last call, and the other
+// one is used once the calls staged there have passed theirs.  A larger buffer
+// replaces one that is too small, also while the caller captures the stream
+// (no event can be waited for then); the old one is kept until the end, at
+// most as much again as the current one, since the size doubles.
+static int stage_pool(Workspace *w, uint64_t words, hipStream_t s) {
+    const bool fits = 2 * words <= w->map_pool_host_cap;
+    if (fits && w->map_pool_pos + words <= w->map_pool_host_cap / 2) return 0;
+    if (!fits || stream_capturing(s)) {
+        const uint64_t cap = std::max<uint64_t>(std::max(2 * words, 2 * w->map_pool_host_cap), 1ull << 16);
+        uint64_t *p = nullptr;
+        HIPCHK(hipHostMalloc((void **)&p, cap * sizeof(uint64_t), hipHostMallocMapped));
+        if (w->map_pool_host) w->map_pool_old.push_back(w->map_pool_host);
+        w->map_pool_host = p;
+        w->map_pool_host_cap = cap;
+        w->map_pool_pos = 0;
+        w->map_pool_half = 0;
+        for (hipEvent_t &e : w->map_ev) {
+            if (e) hipEventDestroy(e);
+            e = nullptr;
+        }
+        return 0;
+    }
+    hipEvent_t &left = w->map_ev[w->map_pool_half];
+    if (!left) HIPCHK(hipEventCreateWithFlags(&left, hipEventDisableTiming));
+    HIPCHK(hipEventRecord(left, s));
+    w->map_pool_half ^= 1;
+    w->map_pool_pos = 0;
+    if (w->map_ev[w->map_pool_half]) HIPCHK(hipEventSynchronize(w->map_ev[w->map_pool_half]));
+    return 0;
+}
+
 // The map launches of devirt_map_pages and devirt_ept_map_pages: workspace,
-// pool upload (pool_gpa: the frames as the caller named them; hpa: their
+// pool staging (pool_gpa: the frames as the caller named them; hpa: their
 // arena offsets, or zeros for frames the device translates), kernels.
 static int map_run(devirt_ctx *c, MapArgs &a, const devirt_map *maps, uint64_t n, const uint64_t *pool_gpa,
                    const std::vector<uint64_t> &hpa, devirt_result *res, uint64_t *n_used, hipStream_t s) {
@@ -696,7 +729,7 @@ static int map_run(devirt_ctx *c, MapArgs &a, const devirt_map *maps, uint64_t n
     };
     const uint32_t tl = log2_for(m + 1), pl = log2_for(n);
     const uint64_t T = 1ull << tl, P = 1ull << pl;
-    const uint64_t words = T + m + P + 4 + m + 2 * n_pool;
+    const uint64_t words = T + m + P + 4 + m + 2 * m;
     int rc;
     if ((rc = grow(c, w, w->map_buf, w->map_cap, words, "map buffers"))) return rc;
     uint64_t *b = w->map_buf;
@@ -716,23 +749,15 @@ static int map_run(devirt_ctx *c, MapArgs &a, const devirt_map *maps, uint64_t n
     a.sc = b + T + m + P;
     a.tkeys_sorted = b + T + m + P + 4;
     a.pool_gpa = b + T + 2 * m + P + 4;
-    a.pool_hpa = b + T + 2 * m + P + 4 + n_pool;
-    if (n_pool) {
-        // staged through pinned memory; the previous upload from it must be done
-        if (w->map_ev) HIPCHK(hipEventSynchronize(w->map_ev));
-        if (w->map_pool_host_cap < 2 * n_pool) {
-            hipHostFree(w->map_pool_host);
-            w->map_pool_host = nullptr;
-            w->map_pool_host_cap = 0;
-            HIPCHK(hipHostMalloc((void **)&w->map_pool_host, 2 * n_pool * sizeof(uint64_t), hipHostMallocDefault));
-            w->map_pool_host_cap = 2 * n_pool;
-        }
-        memcpy(w->map_pool_host, pool_gpa, n_pool * sizeof(uint64_t));
-        memcpy(w->map_pool_host + n_pool, hpa.data(), n_pool * sizeof(uint64_t));
-        HIPCHK(hipMemcpyAsync((void *)a.pool_gpa, w->map_pool_host, 2 * n_pool * sizeof(uint64_t),
-                              hipMemcpyHostToDevice, s));
-        if (!w->map_ev) HIPCHK(hipEventCreateWithFlags(&w->map_ev, hipEventDisableTiming));
-        HIPCHK(hipEventRecord(w->map_ev, s));
+    a.pool_hpa = b + T + 2 * m + P + 4 + m;
+    a.staged = nullptr;
+    if (m) {
+        if ((rc = stage_pool(w, 2 * m, s))) return rc;
+        uint64_t *st = w->map_pool_host + w->map_pool_half * (w->map_pool_host_cap / 2) + w->map_pool_pos;
+        memcpy(st, pool_gpa, m * sizeof(uint64_t));
+        memcpy(st + m, hpa.data(), m * sizeof(uint64_t));
+        w->map_pool_pos += 2 * m;
+        a.staged = st;
     }
     HIPCHK(launch_map(s, a));  // only arena bytes change: captured batch graphs stay valid
     c->xlat_gen++;             // but cached translations may be stale
@@ -749,10 +774,15 @@ int dv_ept_pool_check(const devirt_ctx *c, uint32_t vm, const uint64_t *pool_hos
         if ((pool_host[k] & 0xFFF) || pool_host[k] >= v.bytes || v.bytes - pool_host[k] < 4096)
             return dv_fail(-EINVAL, "pool page %#llx is unaligned or outside the arena",
                            (unsigned long long)pool_host[k]);
-    std::vector<uint64_t> sorted(pool_host, pool_host + n_pool);
-    std::sort(sorted.begin(), sorted.end());
-    if (std::adjacent_find(sorted.begin(), sorted.end()) != sorted.end())
-        return dv_fail(-EINVAL, "pool pages must be distinct");
+    // distinct: a strictly ascending pool (the usual case) needs no sort
+    bool ascending = true;
+    for (uint64_t k = 1; k < n_pool && ascending; ++k) ascending = pool_host[k - 1] < pool_host[k];
+    if (!ascending) {
+        std::vector<uint64_t> sorted(pool_host, pool_host + n_pool);
+        std::sort(sorted.begin(), sorted.end());
+        if (std::adjacent_find(sorted.begin(), sorted.end()) != sorted.end())
+            return dv_fail(-EINVAL, "pool pages must be distinct");
+    }
     return 0;
 }
 

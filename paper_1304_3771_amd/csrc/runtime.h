@@ -58,9 +58,15 @@ struct Workspace {
     // devirt_map_pages
     uint64_t *map_buf = nullptr;        // table-key set and lists, page set, scalars, pool
     uint64_t map_cap = 0;
-    uint64_t *map_pool_host = nullptr;  // pinned staging of the pool (gpa, hpa)
-    uint64_t map_pool_host_cap = 0;
-    hipEvent_t map_ev = nullptr;        // the last pool upload
+    // pinned staging of the pools (gpa, then hpa), read by the calls' first
+    // kernels: two halves, filled in turn; a half is filled again only after
+    // the calls that were staged in it have passed its event
+    uint64_t *map_pool_host = nullptr;
+    std::vector<uint64_t *> map_pool_old;  // outgrown ones, which calls on the stream may still read
+    uint64_t map_pool_host_cap = 0;     // words of both halves
+    uint64_t map_pool_pos = 0;          // words used of half map_pool_half
+    uint32_t map_pool_half = 0;
+    hipEvent_t map_ev[2] = {nullptr, nullptr};  // the last call staged in the half has read it
     ~Workspace();
 };
 
