@@ -218,7 +218,9 @@ struct PlainArgs {
     uint32_t code0;     // known before the walk: unknown process, range not user-canonical
     uint32_t inline_copy;
     uint32_t nontemporal;
-    uint32_t pad;
+    uint32_t fifo_entries;  // 0: no translation cache
+    DFifo *fifo;            // the process's
+    uint64_t xlat_gen;
 };
 constexpr uint32_t kPlainWaves = 16;  // wavefronts of the one workgroup, at most
 

@@ -1564,12 +1564,96 @@ __device__ __forceinline__ void page_walk(const DVm &vm, const SlotLanes &sl, co
 // so a last region that starts in lane 31 or later gets its accessed and dirty
 // bits above level 1 only from a pass that continues it.  The kernels that took
 // over its requests one at a time leave out the same bits: whether this lane's
-// page lies in such a region.  Pages [first, last] of the request are the
-// pass's.  To be mended in all of them at once.
-__device__ __forceinline__ bool last_head_lost(uint64_t gva, uint32_t first, uint32_t last) {
-    const uint64_t p0 = gva >> 12, region = (p0 + last) & ~511ull;  // the last region's first page
-    const uint64_t head = region > p0 + first ? region - (p0 + first) : 0;
-    return head >= 31 && (uint64_t)lane_id() >= head;
+// page lies in such a region.  A pass is 64 consecutive pages, a lane each; a
+// region starts anew behind a page that is not walked.  To be mended in all of
+// them at once.
+__device__ __forceinline__ bool last_head_lost(uint64_t gva, bool walked) {
+    const int lane = lane_id();
+    const uint64_t wm = __ballot(walked), p = gva >> 12;
+    const bool head = walked && (lane == 0 || !((wm >> (lane - 1)) & 1) || ((p - 1) ^ p) >> 9 != 0);
+    const uint64_t heads = __ballot(head);
+    const int last = heads ? 63 - __clzll(heads) : 0;
+    return last >= 31 && lane >= last;
+}
+
+// The process's translation cache as one request finds it (section 4.2): a
+// FIFO whose slots lie in lanes 0..cap-1 of every wavefront.  The request's
+// pages are distinct and ascend, so what a lookup in page order finds depends
+// on the slots held before it alone: every page that was not held when its
+// turn came is inserted, and slot q of the queue leaves with insertion number
+// cap - n + q + 1.
+struct FifoLook {
+    uint64_t gen;
+    uint64_t v, h;           // the lane's slot: page number, arena offset of the page
+    uint32_t idx;            // the request's page that it holds (kNone: none of them)
+    uint32_t n, head, written, cap;
+    uint64_t hits, misses;   // counted so far
+    uint64_t held;           // slots that are held when their page's turn comes
+    uint64_t hit;            // slots whose page is not walked
+};
+
+// Pages inserted before page i's turn (uniform).
+__device__ __forceinline__ uint32_t fifo_inserts(const FifoLook &f, uint32_t i) {
+    return i - (uint32_t)__popcll(f.held & __ballot(f.idx < i));
+}
+
+__device__ __forceinline__ void fifo_load(const PlainArgs &a, FifoLook &f) {
+    const uint32_t lane = (uint32_t)lane_id();
+    const DFifo *q = a.fifo;
+    f.gen = *gp<const g_u64>(&q->gen);
+    f.n = *gp<const g_u32>(&q->n);
+    f.head = *gp<const g_u32>(&q->head);
+    f.written = *gp<const g_u32>(&q->written);
+    f.hits = *gp<const DV_GLOBAL unsigned long long>(&q->hits);
+    f.misses = *gp<const DV_GLOBAL unsigned long long>(&q->misses);
+    f.v = ~0ull;
+    f.h = 0;
+    if (lane < a.fifo_entries) {
+        f.v = gp<const g_u64>(q->vpn)[lane];
+        f.h = gp<const g_u64>(q->hpa)[lane];
+    }
+}
+
+__device__ __forceinline__ void fifo_look(const PlainArgs &a, uint32_t total, FifoLook &f) {
+    const uint32_t lane = (uint32_t)lane_id(), cap = a.fifo_entries;
+    f.cap = cap;
+    f.n = uniform_u32(f.n);
+    f.head = uniform_u32(f.head);
+    f.written = uniform_u32(f.written);
+    if (uniform_u64(f.gen) != a.xlat_gen) f.n = f.head = f.written = 0;  // emptied since
+    if (f.n > cap) {  // it had more slots: the ones that are left, oldest first
+        f.head += f.n;
+        f.n = cap;
+    }
+    if (f.head >= cap) f.head %= cap;
+    const uint32_t place = lane >= f.head ? lane - f.head : lane + cap - f.head;  // in the queue, oldest first
+    const uint64_t d = f.v - (a.gva >> 12);
+    const bool in = lane < cap && place < f.n && d < total;
+    f.idx = in ? (uint32_t)d : kNone;
+    f.held = f.hit = 0;
+    const uint64_t im = __ballot(in);
+    if (!im) return;
+    uint32_t rank = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kFifoMax; ++k)
+        rank += (uint32_t)__builtin_amdgcn_readlane((int)f.idx, (int)k) < f.idx ? 1u : 0u;
+    const uint32_t leaves = cap - f.n + place + 1;
+    // held, were every slot before it held: most often so, or none after it is
+    f.held = __ballot(in && f.idx - rank < leaves);
+    const uint32_t held = (uint32_t)__popcll(f.held);
+    if (__ballot(((f.held >> lane) & 1) && rank >= held)) {
+        f.held = 0;
+        for (uint32_t r = 0; r < (uint32_t)__popcll(im); ++r)  // in page order
+            f.held |= __ballot(in && rank == r && f.idx - (uint32_t)__popcll(f.held) < leaves);
+    }
+    // a page is left unwalked if its slot is held as the page's pass of 64 begins
+    uint64_t pass = f.held;
+    for (uint64_t m = im & ~f.held; m; m &= m - 1) {
+        const int k = __ffsll((unsigned long long)m) - 1;
+        const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)f.idx, k) & ~63u;
+        if (fifo_inserts(f, first) < (uint32_t)__builtin_amdgcn_readlane((int)leaves, k)) pass |= 1ull << k;
+    }
+    f.hit = a.dir ? pass & f.written : pass;
 }
 
 // Shared state of k_plain_walk's workgroup.
@@ -1579,15 +1663,17 @@ struct PlainShared {
     uint32_t ff;                      // the request's first faulting page (kNone: none)
     uint32_t fcode, flevel;
     uint64_t flo;
+    uint64_t fifo_v[kFifoMax], fifo_h[kFifoMax];  // what each slot of the translation cache was given last
 };
 
-template <int LEVELS>
-__device__ void plain_pages(const PlainArgs &a, const DVm &vm, const SlotLanes &sl, PlainShared &sh) {
+template <int LEVELS, bool FIFO>
+__device__ void plain_pages(const PlainArgs &a, const DVm &vm, const SlotLanes &sl, FifoLook &fifo, PlainShared &sh) {
     const int lane = lane_id();
     const uint32_t wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
     const uint64_t end = a.gva + a.len;
     const uint32_t total = (uint32_t)(((end - 1) >> 12) - (a.gva >> 12) + 1);
     uint32_t ff = kNone;
+    if (FIFO) fifo_look(a, total, fifo);
     for (uint32_t base = 0; base < total && ff == kNone; base += 64 * waves) {
         const uint32_t c = base + threadIdx.x;
         const uint64_t page = (a.gva & ~0xFFFull) + ((uint64_t)c << 12);
@@ -1596,8 +1682,28 @@ __device__ void plain_pages(const PlainArgs &a, const DVm &vm, const SlotLanes &
         PageWalk<LEVELS> w;
         w.code = DEVIRT_OK;
         w.leaf = 0;
-        if (base + 64 * wave < total)
-            page_walk<LEVELS>(vm, sl, sh.slots, a.cr3, lo, a.dir != 0, act, w);
+        bool walk = act;
+        uint64_t held = 0;  // which of the 64 pages are held when their turn comes
+        if (FIFO) {
+            const uint32_t at = fifo.idx - (base + 64 * wave);
+            const uint64_t here = (fifo.held | fifo.hit) & __ballot(fifo.idx != kNone && at < 64);
+            uint64_t hit = 0;
+            for (uint64_t m = here; m; m &= m - 1) {
+                const int k = __ffsll((unsigned long long)m) - 1;
+                const int l = __builtin_amdgcn_readlane((int)at, k);
+                held |= ((fifo.held >> k) & 1) << l;
+                hit |= ((fifo.hit >> k) & 1) << l;
+            }
+            if (hit) {  // their places go from the slots' lanes to the pages'
+                walk = act && !((hit >> lane) & 1);
+                if ((here & fifo.hit) >> lane & 1) sh.page[64 * wave + at] = fifo.h;
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+        if (FIFO ? __ballot(walk) != 0 : base + 64 * wave < total)
+            page_walk<LEVELS>(vm, sl, sh.slots, a.cr3, lo, a.dir != 0, walk, w);
+        if (FIFO && act && !walk) w.hpa = sh.page[threadIdx.x] + (lo & 0xFFFull);
         // the first fault of the round, agreed before any byte or bit changes
         const uint64_t fm = __ballot(act && w.code != DEVIRT_OK);
         if (fm && lane == 0) atomicMin(&sh.ff, base + 64 * wave + (uint32_t)__ffsll((unsigned long long)fm) - 1);
@@ -1632,24 +1738,58 @@ __device__ void plain_pages(const PlainArgs &a, const DVm &vm, const SlotLanes &
         // A/D of the copied pages' paths: an entry shared with the previous
         // lane is left to that lane
         if (base + 64 * wave < stop) {
-            const uint32_t p0 = base + 64 * wave;
-            const bool lost = last_head_lost(a.gva, p0, p0 + 64 < total ? p0 + 63 : total - 1);
+            const bool lost = last_head_lost(page, walk);
 #pragma unroll
             for (int i = 0; i < LEVELS; ++i) {
                 const int lvl = LEVELS - i;
                 const uint64_t prev = shfl64(w.off[i], lane > 0 ? lane - 1 : 0);
                 if (LEVELS == 3 && lvl == 3) continue;
                 const uint32_t want = (uint32_t)kA | (w.leaf == (uint32_t)lvl && a.dir ? (uint32_t)kD : 0u);
-                if (act && c < stop && lvl >= (int)w.leaf && (lane == 0 || prev != w.off[i]) &&
+                if (walk && c < stop && lvl >= (int)w.leaf && (lane == 0 || prev != w.off[i]) &&
                     (w.lo[i] & want) != want && !(lvl > 1 && lost))
                     or_entry(vm.arena, w.off[i], want);
+            }
+            if (FIFO) {  // the last pages inserted so far, each in its slot
+                const uint32_t to = stop < base + 64 * waves ? stop : base + 64 * waves;
+                const bool near = act && c < to && !((held >> lane) & 1) && c + 2 * fifo.cap >= to;
+                if (__ballot(near)) {
+                    const uint32_t t = fifo_inserts(fifo, base + 64 * wave) + (uint32_t)lane -
+                                       (uint32_t)__popcll(held & mask_lt(lane));
+                    if (near && t + fifo.cap >= fifo_inserts(fifo, to)) {
+                        const uint32_t slot = (fifo.head + fifo.n + t) % fifo.cap;
+                        sh.fifo_v[slot] = page >> 12;
+                        sh.fifo_h[slot] = w.hpa - (lo & 0xFFFull);
+                    }
+                }
             }
         }
         if (base + 64 * waves < total) __syncthreads();  // sh.page and sh.ff are used again
     }
     if (!a.inline_copy && threadIdx.x < 2 * kQParts)
         a.ctr->q[threadIdx.x][0] = threadIdx.x ? 0 : (ff < total ? ff : total);
-    if (ff != kNone) __syncthreads();  // workgroup-uniform
+    if (FIFO || ff != kNone) __syncthreads();  // workgroup-uniform
+    if (FIFO && wave == 0) {
+        const uint32_t cap = fifo.cap, stop = ff < total ? ff : total, seen = ff < total ? ff + 1 : total;
+        const uint32_t ins = fifo_inserts(fifo, stop), l = (uint32_t)lane;
+        const bool mine = (fifo.held >> lane) & 1, wr = (fifo.written >> (l & 31)) & 1;
+        const uint32_t hits = (uint32_t)__popcll(__ballot(mine && fifo.idx < seen && (!a.dir || wr)));
+        const bool fresh = l < cap && (ins >= cap || (l + 2 * cap - (fifo.head + fifo.n) % cap) % cap < ins);
+        const uint64_t wm = __ballot(l < cap && (fresh ? a.dir != 0 : wr || (a.dir && mine && fifo.idx < stop)));
+        DFifo *q = a.fifo;
+        if (l < cap) {
+            gp<g_u64>(q->vpn)[l] = fresh ? sh.fifo_v[l] : fifo.v;
+            gp<g_u64>(q->hpa)[l] = fresh ? sh.fifo_h[l] : fifo.h;
+        }
+        if (lane == 0) {
+            const uint32_t all = fifo.n + ins;
+            *gp<g_u32>(&q->written) = (uint32_t)wm;
+            *gp<g_u32>(&q->n) = all < cap ? all : cap;
+            *gp<g_u32>(&q->head) = all > cap ? (fifo.head + (all - cap)) % cap : fifo.head;
+            *gp<g_u64>(&q->gen) = a.xlat_gen;
+            *gp<DV_GLOBAL unsigned long long>(&q->hits) = fifo.hits + hits;
+            *gp<DV_GLOBAL unsigned long long>(&q->misses) = fifo.misses + (seen - hits);
+        }
+    }
     if (threadIdx.x == 0) {
         devirt_result r;
         r.pad = 0;
@@ -1675,6 +1815,13 @@ __device__ void plain_pages(const PlainArgs &a, const DVm &vm, const SlotLanes &
 // and copied it alone up to 16 pages: 24 B 8.2 -> 5.5 us, 32 KiB 13.4 -> 5.8,
 // 100 KB 12.7 -> 6.7, 1 MiB 29.7 -> 8.8, 4,147,200 B 76.9 -> 10.2; behind an
 // EPT 24 B 8.9 -> 7.0, 4,147,200 B 88.8 -> 13.6.
+//
+// FIFO: with the process's translation cache.  Its lookups one after the other
+// (a ballot and a dozen steps a page, by one wavefront) are replaced by what
+// they come to, see FifoLook; back-to-back calls, 10 entries: 24 B that are
+// held 7.4 -> 4.8 us, 32 KiB held 11.4 -> 5.4, 100 KB 25.9 -> 9.0, 1 MiB 111.6
+// -> 11.7, 4,147,200 B 377.7 -> 14.3, behind an EPT 396.9 -> 17.6.
+template <bool FIFO>
 __global__ void __launch_bounds__(64 * kPlainWaves) k_plain_walk(PlainArgs a) {
     __shared__ PlainShared sh;
     if (a.code0 || a.len == 0) {
@@ -1697,15 +1844,17 @@ __global__ void __launch_bounds__(64 * kPlainWaves) k_plain_walk(PlainArgs a) {
     sl.end = row[lane_id()].end;
     sl.off = row[lane_id()].arena_off;
     const DVm vm = load_vm(a.v, a.vm, false);
+    FifoLook fifo;
+    if (FIFO) fifo_load(a, fifo);  // with the VM's record, not behind it
     if (threadIdx.x < kSlotRow) sh.slots[threadIdx.x] = DSlot{sl.gpa, sl.end, sl.off};
     if (threadIdx.x == 0) sh.ff = kNone;
     __syncthreads();
     if (a.levels == 5)
-        plain_pages<5>(a, vm, sl, sh);
+        plain_pages<5, FIFO>(a, vm, sl, fifo, sh);
     else if (a.levels == 4)
-        plain_pages<4>(a, vm, sl, sh);
+        plain_pages<4, FIFO>(a, vm, sl, fifo, sh);
     else
-        plain_pages<3>(a, vm, sl, sh);
+        plain_pages<3, FIFO>(a, vm, sl, fifo, sh);
 }
 
 // ------------------------------------------- small batches, one request a wave
@@ -1768,8 +1917,7 @@ __device__ uint32_t one_pages(const DBatch &b, const DVm &vm, const SlotLanes &s
     }
     // A/D of the copied pages' paths, while the queue places are on their way:
     // an entry shared with the previous lane is left to that lane
-    const uint32_t p0 = base + 64 * part;
-    const bool lost = last_head_lost(gva, p0, p0 + 64 < total ? p0 + 63 : total - 1);
+    const bool lost = last_head_lost(page, act);
 #pragma unroll
     for (int i = 0; i < LEVELS; ++i) {
         const int lvl = LEVELS - i;
@@ -2432,7 +2580,7 @@ hipError_t launch_spill(hipStream_t s, int grid, int block, DView v, DBatch b, u
 }
 
 hipError_t launch_plain_walk(hipStream_t s, uint32_t waves, const PlainArgs &a) {
-    hipLaunchKernelGGL(k_plain_walk, dim3(1), dim3(64 * waves), 0, s, a);
+    hipLaunchKernelGGL(a.fifo_entries ? k_plain_walk<true> : k_plain_walk<false>, dim3(1), dim3(64 * waves), 0, s, a);
     return hipGetLastError();
 }
 

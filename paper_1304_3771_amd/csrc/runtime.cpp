@@ -877,9 +877,9 @@ int plain_copy(devirt_ctx *c, uint32_t asid, uint64_t gva, uint64_t host, uint64
     if (st && pages > st->cap)  // the caller's static scratch: nothing is allocated
         return dv_fail(-EINVAL, "the request touches %llu pages; this entry point takes at most %llu",
                        (unsigned long long)pages, (unsigned long long)st->cap);
-    // The translation cache and the device counters belong to the walk by one
-    // wavefront (k_plain); every other request is walked by k_plain_walk.
-    const bool one_wave = c->cfg.fifo_entries != 0 || (c->profiling & DEVIRT_PROF_COUNTERS);
+    // The device counters belong to the walk by one wavefront (k_plain); every
+    // other request is walked by k_plain_walk.
+    const bool one_wave = (c->profiling & DEVIRT_PROF_COUNTERS) != 0;
     const bool inl = pages <= kPlainInlinePages;
     int rc;
     DBatch b;
@@ -938,6 +938,11 @@ int plain_copy(devirt_ctx *c, uint32_t asid, uint64_t gva, uint64_t host, uint64
             a.levels = p.levels;
             a.cr3 = p.cr3;
             a.code0 = range_code(gva, len, p.levels);
+            if (c->cfg.fifo_entries) {
+                a.fifo = c->d_fifo + asid;
+                a.fifo_entries = c->cfg.fifo_entries;
+                a.xlat_gen = c->xlat_gen;
+            }
         }
         // inline: a wavefront per page to copy; else one per 64 pages to walk
         const uint64_t waves = a.code0 ? 1 : inl ? pages : (pages + 63) / 64;
