@@ -1576,6 +1576,20 @@ __device__ __forceinline__ bool last_head_lost(uint64_t gva, bool walked) {
     return last >= 31 && lane >= last;
 }
 
+// The same for page c of a request that shared process_group's passes with the
+// others of its group: the request's pages have places [start, start + total)
+// among the group's; follows: a later request of the group has pages, which
+// then begin at start + total.
+__device__ __forceinline__ bool last_head_lost(uint64_t gva, uint32_t c, uint32_t total, uint32_t start, bool follows) {
+    const uint32_t p = start + c, pass = p & ~63u, end = start + total;
+    if (follows && end <= pass + 63) return false;
+    const uint32_t first = start > pass ? start : pass, last = end - 1 < pass + 63 ? end - 1 : pass + 63;
+    const uint64_t p0 = gva >> 12, region = (p0 + (last - start)) & ~511ull;  // the last region's first page
+    const uint32_t r = start + (region > p0 ? (uint32_t)(region - p0) : 0u);
+    const uint32_t head = (r > first ? r : first) - pass;
+    return head >= 31 && p - pass >= head;
+}
+
 // The process's translation cache as one request finds it (section 4.2): a
 // FIFO whose slots lie in lanes 0..cap-1 of every wavefront.  The request's
 // pages are distinct and ascend, so what a lookup in page order finds depends
@@ -1871,7 +1885,8 @@ struct OneFault {
 template <int LEVELS>
 __device__ uint32_t one_pages(const DBatch &b, const DVm &vm, const SlotLanes &sl, const DSlot *slots, uint64_t cr3,
                               uint64_t gva, uint64_t host, uint32_t len, bool dir, uint32_t req, uint32_t total,
-                              uint32_t base, uint32_t part, uint32_t qpart, bool direct, uint32_t *ff, OneFault *f) {
+                              uint32_t start, bool follows, uint32_t base, uint32_t part, uint32_t qpart, bool direct,
+                              uint32_t *ff, OneFault *f) {
     const int lane = lane_id();
     const uint32_t c = base + 64 * part + (uint32_t)lane;
     const uint64_t end = gva + len;
@@ -1917,14 +1932,15 @@ __device__ uint32_t one_pages(const DBatch &b, const DVm &vm, const SlotLanes &s
     }
     // A/D of the copied pages' paths, while the queue places are on their way:
     // an entry shared with the previous lane is left to that lane
-    const bool lost = last_head_lost(page, act);
+    const bool lost = last_head_lost(gva, c, total, start, follows);
+    const bool lost_before = ((__ballot(lost) << 1) >> lane) & 1;
 #pragma unroll
     for (int i = 0; i < LEVELS; ++i) {
         const int lvl = LEVELS - i;
         const uint64_t po = shfl64(w.off[i], lane > 0 ? lane - 1 : 0);
         if (LEVELS == 3 && lvl == 3) continue;
         const uint32_t want = (uint32_t)kA | (w.leaf == (uint32_t)lvl && dir ? (uint32_t)kD : 0u);
-        if (copied && lvl >= (int)w.leaf && (lane == 0 || po != w.off[i]) && (w.lo[i] & want) != want &&
+        if (copied && lvl >= (int)w.leaf && (lane == 0 || po != w.off[i] || lost_before) && (w.lo[i] & want) != want &&
             !(lvl > 1 && lost))
             or_entry(vm.arena, w.off[i], want);
     }
@@ -1956,7 +1972,7 @@ __device__ uint32_t one_pages(const DBatch &b, const DVm &vm, const SlotLanes &s
     return first;
 }
 
-// A one-epoch batch so small that a wavefront can have each request to itself.
+// A one-epoch batch so small that each request can have a wavefront to itself.
 // Bound by the latency of one wavefront: its own instructions and cross-lane
 // steps as much as its loads.  k_translate_groups spends about 1,200 vector
 // instructions and 92 LDS operations on a wavefront's first pass, most of them
@@ -1964,9 +1980,11 @@ __device__ uint32_t one_pages(const DBatch &b, const DVm &vm, const SlotLanes &s
 // here the request is the wavefront's, its fields are scalars, and the walk is
 // that of the per-request copy.  A request of more than kOneAlone pages is
 // walked by the workgroup's wavefronts together, 64 pages each a round.
-// Batches in us, k_translate_groups and this: 256 requests of up to 4 KiB 17.3
-// and 12.4, 2,000 of up to 64 KiB behind an EPT 23.2 and 19.9, 1,000 of up to
-// 1 MiB 39.9 and 33.3, 8,191 of up to 64 KiB 37.2 and 36.2.
+// The rest of a request's group is looked at only for the accessed bits that
+// it would have been left without there, see last_head_lost.  The kernel's
+// time in us, k_translate_groups and this: 2,048 requests, one in a hundred of
+// 4,147,200 bytes, 78.2 and 28.9; 8,191 of up to 64 KiB 15.3 and 17.1, which
+// is why larger batches are not translated so.
 constexpr uint32_t kOneAlone = 128;
 struct OneShared {
     DSlot slots[4][kSlotRow];
@@ -1997,11 +2015,21 @@ __global__ void __launch_bounds__(256) k_translate_one(DView v, DBatch b, uint64
     __syncthreads();
     // one request: of this wavefront (team == 0), or of the workgroup
     const auto translate = [&](uint64_t i, uint32_t part, uint32_t team) {
-        const g_u32x4 *p = gp<const g_u32x4>(b.reqs + i);
-        const u32x4 qa = p[0], qb = p[1];
-        const uint64_t gva = uniform_u64(((uint64_t)qa.y << 32) | qa.x), host = uniform_u64(((uint64_t)qa.w << 32) | qa.z);
-        const uint32_t len = uniform_u32(qb.x), asid = uniform_u32(qb.y);
-        const bool dir = (uniform_u32(qb.z) & 0xFF) != 0;
+        // the requests of its group, a lane each, for the places of its pages
+        const int own = b.group == 1 ? 0 : (int)((uint32_t)i % b.group);
+        const uint64_t g0 = i - (uint64_t)own;
+        const uint32_t gn = n - g0 < b.group ? (uint32_t)(n - g0) : b.group;
+        u32x4 qa{0, 0, 0, 0}, qb{0, 0, 0, 0};
+        if ((uint32_t)lane < gn) {
+            const g_u32x4 *p = gp<const g_u32x4>(b.reqs + g0) + 2 * lane;
+            qa = p[0];
+            qb = p[1];
+        }
+        const auto mine32 = [&](uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)x, own); };
+        const uint64_t gva = ((uint64_t)mine32(qa.y) << 32) | mine32(qa.x);
+        const uint64_t host = ((uint64_t)mine32(qa.w) << 32) | mine32(qa.z);
+        const uint32_t len = mine32(qb.x), asid = mine32(qb.y);
+        const bool dir = (mine32(qb.z) & 0xFF) != 0;
         uint32_t code0 = DEVIRT_OK, ff = kNone;
         OneFault f{0, 0, 0};
         if (asid >= v.nproc) {
@@ -2014,6 +2042,19 @@ __global__ void __launch_bounds__(256) k_translate_one(DView v, DBatch b, uint64
                 code0 = DEVIRT_NONCANONICAL;
             } else {
                 const uint32_t total = (uint32_t)(((gva + len - 1) >> 12) - (gva >> 12) + 1);
+                uint32_t start = 0;
+                bool follows = false;
+                if (gn > 1) {
+                    const uint64_t og = ((uint64_t)qa.y << 32) | qa.x;
+                    uint32_t pages = 0;
+                    if ((uint32_t)lane < gn && qb.y < v.nproc && qb.x) {
+                        const uint64_t ol = user_limit(gp<const DV_GLOBAL DProc>(v.procs)[qb.y].levels);
+                        if (og < ol && (uint64_t)qb.x <= ol - og)
+                            pages = (uint32_t)(((og + qb.x - 1) >> 12) - (og >> 12) + 1);
+                    }
+                    for (int k = 0; k < own; ++k) start += (uint32_t)__builtin_amdgcn_readlane((int)pages, k);
+                    follows = (__ballot(pages != 0) & ~mask_le(own)) != 0;
+                }
                 if (!team && waves > 1 && total > kOneAlone) {
                     if (lane == 0) sh.big[wave] = 1;
                     return;
@@ -2035,14 +2076,14 @@ __global__ void __launch_bounds__(256) k_translate_one(DView v, DBatch b, uint64
                     uint32_t *sf = team ? &sh.ff : nullptr;
                     OneFault *out = team ? fo : &mine;
                     if (levels == 5)
-                        ff = one_pages<5>(b, vm, sl, slots, cr3, gva, host, len, dir, (uint32_t)i, total, base, part,
-                                          qpart, direct != 0, sf, out);
+                        ff = one_pages<5>(b, vm, sl, slots, cr3, gva, host, len, dir, (uint32_t)i, total, start,
+                                          follows, base, part, qpart, direct != 0, sf, out);
                     else if (levels == 4)
-                        ff = one_pages<4>(b, vm, sl, slots, cr3, gva, host, len, dir, (uint32_t)i, total, base, part,
-                                          qpart, direct != 0, sf, out);
+                        ff = one_pages<4>(b, vm, sl, slots, cr3, gva, host, len, dir, (uint32_t)i, total, start,
+                                          follows, base, part, qpart, direct != 0, sf, out);
                     else
-                        ff = one_pages<3>(b, vm, sl, slots, cr3, gva, host, len, dir, (uint32_t)i, total, base, part,
-                                          qpart, direct != 0, sf, out);
+                        ff = one_pages<3>(b, vm, sl, slots, cr3, gva, host, len, dir, (uint32_t)i, total, start,
+                                          follows, base, part, qpart, direct != 0, sf, out);
                     if (team) __syncthreads();  // ff is read by every wavefront before the next round adds to it
                 }
                 if (ff != kNone) {

@@ -1023,15 +1023,15 @@ static hipError_t spill_pass(devirt_ctx *c, hipStream_t st, const DView &v, cons
                         (int)c->cfg.xlat_wg, v, be, r0, r1, (uint32_t)e);
 }
 
-// A one-epoch batch whose groups are single requests (up to 4 per CU, unless
-// configured so) is translated by k_translate_one: 256 requests of up to 4 KiB
-// 17.3 us a batch in groups, 12.4 so, 1,000 of up to 1 MiB 39.9 and 33.3.  (The
-// walk by large_pages and the device counters belong to k_translate_groups.)
-// With configured groups of one, more wavefronts than about twice what the
-// chip holds lose: 12,000 requests of up to 4 KiB 24.0 us in groups, 31.7 so.
-// Between 1,024 and 8,192 requests it would gain 1-3 us too, but there it would
-// change which accessed bits a batch leaves unset (see last_head_lost).
-static const uint64_t kOneMax = 8192;
+// A one-epoch batch is translated by k_translate_one, a wavefront per request,
+// while the chip holds all of them at once (its registers allow 16 a CU).
+// Batch times in us, in groups and so: 256 requests of up to 4 KiB 17.3 and
+// 12.4, 1,000 of up to 1 MiB 39.9 and 33.3, 2,048 of up to 4 KiB, 64 KiB and
+// 1 MiB 17.1 / 20.9 / 60.4 and 13.7 / 17.7 / 51.7, 4,000 of up to 64 KiB 24.3
+// and 22.2; beyond, wavefronts queue for a place: 5,000 26.7 and 29.2, 8,191
+// 37.2 and 38.7.  (The walk by large_pages and the device counters belong to
+// k_translate_groups.)
+static const uint64_t kOnePerCu = 16;
 
 // The ordered fault list: a tile count, a scan, a scatter.
 static int fault_list(Workspace *w, const BatchArgs &a, hipStream_t s) {
@@ -1077,7 +1077,7 @@ static int enqueue_batch(devirt_ctx *c, Workspace *w, const BatchArgs &a, hipStr
         CopyTail tail{a.n, list ? nullptr : a.faults, list ? nullptr : a.n_faults, w->ctr + (w->ctr_turn ^ 1)};
         ProfEv *pe;
         int rc;
-        const bool one = b.group == 1 && a.n <= kOneMax && !b.large_pages && !b.counters;
+        const bool one = a.n <= kOnePerCu * c->cus && !b.large_pages && !b.counters;
         if ((rc = prof_begin(c, s, 1, &pe))) return rc;
         if (one)
             HIPCHK(launch_translate_one(s, (int)c->cfg.xlat_wg, v, b, a.n, 0));

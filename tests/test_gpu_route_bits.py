@@ -51,3 +51,48 @@ def test_routes_leave_the_same_bits(levels):
         bad = [int((a.view(np.uint8) != b.view(np.uint8)).sum()) for a, b in zip(got, seen["plain"])]
         log(f"levels {levels}, {name}: bytes that differ from the per-request copies' {bad}")
         assert bad == [0, 0, 0]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,levels,vms",
+                         [(1024, 4, 1), (1025, 5, 2), (2049, 3, 1), (3073, 4, 4), (4096, 4, 1), (4097, 5, 1)])
+def test_small_batches_leave_the_same_bits(n, levels, vms):
+    """A one-epoch batch, whose requests a wavefront (or a workgroup: the long ones) walks one by one up to 4,096,
+    and the same batch walked in groups, as it is while the device counters are on."""
+    import torch  # noqa: F401  (the HIP runtime that the library then shares)
+    sp = gen.spec("C1", mem_bytes=256 * MiB, levels=levels, n_vms=vms, mix=(0.75, 0.25, 0.0), p_np=0.001, rho=0.5,
+                  vmas_per_proc=4, n_requests=n, len_lo=24, len_hi=16384, seed=4900 + n)
+    w = gen.make_workload(sp)
+    rng = np.random.default_rng(n)
+    r = w.requests.copy()
+    # one epoch: the odd VMAs are written, each page by one request, the even ones read
+    written = set()
+    for i, (asid, gva, ln) in enumerate(zip(r["asid"].tolist(), r["gva"].tolist(), r["len"].tolist())):
+        vma = next(k for k, (b, s) in enumerate(w.procs[asid].vmas.tolist()) if b <= gva < b + s)
+        r["dir"][i] = vma & 1
+        pages = {(asid, p) for p in range(gva >> 12, ((gva + max(ln, 1) - 1) >> 12) + 1)}
+        if vma & 1 and pages & written:
+            r["len"][i] = 0
+        elif vma & 1:
+            written |= pages
+    big = np.flatnonzero((rng.random(n) < 0.04) & (r["dir"] == 0))[:150]  # up to 2.5 MiB
+    for i in big:
+        base, size = (int(x) for x in w.procs[int(r["asid"][i])].vmas[0])
+        ln = int(rng.integers(60, 640)) * 4096
+        r["gva"][i] = base + int(rng.integers(0, size - ln))
+        r["len"][i] = ln
+    r["host"] = np.concatenate([[0], np.cumsum(r["len"].astype(np.uint64))[:-1]])
+    w.requests, w.epoch_end, w.pool_bytes = r, np.array([n], np.uint64), (int(r["len"].sum()) + 4095) & ~4095
+    seen = []
+    for counters in (False, True):
+        ctx = new_ctx()
+        try:
+            dw = device.load(ctx, w)
+            ctx.set_profiling(counters, counters=counters)
+            res, faults, arenas, pool, _ = gpu_batch(w, ctx=ctx, dw=dw)
+            seen.append((res, faults, pool, *arenas))
+        finally:
+            ctx.close()
+    bad = [int((a.view(np.uint8) != b.view(np.uint8)).sum()) for a, b in zip(*seen)]
+    log(f"{n} requests, {len(big)} long, {len(seen[0][1])} faults: bytes that differ {bad}")
+    assert bad == [0] * len(bad)
