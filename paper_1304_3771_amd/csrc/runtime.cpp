@@ -858,6 +858,12 @@ static uint64_t pages_of(uint64_t gva, uint64_t len) {
 // against 8.1, 200 KB (49 pages) 8.4 against 8.3, 512 KiB 9.4 against 8.6.
 static const uint64_t kPlainInlinePages = 40;
 
+// The workgroup of a copy that the chip holds all wavefronts of (32 per CU):
+// smaller ones spread it over more CUs and start and end sooner.  Per-request
+// copies in workgroups of 1024 and of 256: 170 KB 9.7 and 9.3 us, 1 MiB 10.4
+// and 9.8, 4,147,200 B 11.8 and 11.3, 8 MiB 20.0 and 19.6.
+static const uint32_t kCopyShortWg = 256;
+
 // The range check of a request of a process with `levels`-deep tables.
 static uint32_t range_code(uint64_t gva, uint64_t len, uint32_t levels) {
     const uint64_t lim = levels == 5 ? 1ull << 56 : levels == 3 ? 1ull << 32 : 1ull << 47;
@@ -951,7 +957,8 @@ int plain_copy(devirt_ctx *c, uint32_t asid, uint64_t gva, uint64_t host, uint64
     if (!inl) {
         ProfEv *pe = nullptr;
         if (!st && (rc = prof_begin(c, s, 0, &pe))) return rc;
-        HIPCHK(launch_copy(s, grid_for(c, pages, c->cfg.copy_wg, c->cfg.copy_wgs_per_cu), c->cfg.copy_wg, b, 0));
+        const uint32_t wg = pages <= 32ull * c->cus ? std::min(c->cfg.copy_wg, kCopyShortWg) : c->cfg.copy_wg;
+        HIPCHK(launch_copy(s, grid_for(c, pages, wg, c->cfg.copy_wgs_per_cu * (c->cfg.copy_wg / wg)), wg, b, 0));
         if ((rc = prof_end(c, s, pe))) return rc;
     }
     return 0;
@@ -994,16 +1001,21 @@ static uint32_t epoch_group(const devirt_ctx *c, uint64_t n) {
     return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(c->cfg.group, spread));
 }
 
-// The copy grid of an epoch of n requests: the configured one, but for at most
-// 8192 requests no more than 4 wavefronts each (at least 32 per CU, which fill
-// the chip).  Such an epoch's copy is so short that launching the whole grid
-// shows in it: 8,191 requests of up to 64 KiB 59 us a batch with 16 workgroups
-// of 1024 per CU, 56 with 8.
-static int copy_grid(const devirt_ctx *c, uint64_t n) {
-    const uint64_t wpb = c->cfg.copy_wg / 64, most = (uint64_t)c->cus * c->cfg.copy_wgs_per_cu;
-    if (n > 8192) return (int)most;
-    const uint64_t waves = std::max<uint64_t>(4 * n, 32ull * c->cus);
-    return (int)std::min<uint64_t>(most, (waves + wpb - 1) / wpb);
+// The copy launch of an epoch of n requests: the configured one, but for at
+// most 8192 requests no more than 4 wavefronts each (at least 32 per CU, which
+// fill the chip).  Such an epoch's copy is so short that launching the whole
+// grid shows in it: 8,191 requests of up to 64 KiB 59 us a batch with 16
+// workgroups of 1024 per CU, 56 with 8.  At most one request per CU: half as
+// many wavefronts, in workgroups of 256, which start and end sooner: 256
+// requests of up to 4 KiB, 64 KiB and 1 MiB 12.8 / 13.4 / 22.7 us a batch in
+// 1024s, 12.2 / 12.4 / 22.2 so (1,000 of up to 1 MiB lose: 32.6 and 33.2).
+static hipError_t launch_epoch_copy(const devirt_ctx *c, hipStream_t s, const DBatch &b, uint64_t n, uint32_t epoch,
+                                    const CopyTail &tail = CopyTail{}) {
+    const bool few = n <= (uint64_t)c->cus;
+    const uint64_t block = few ? std::min<uint64_t>(c->cfg.copy_wg, kCopyShortWg) : c->cfg.copy_wg, wpb = block / 64;
+    const uint64_t most = (uint64_t)c->cus * c->cfg.copy_wgs_per_cu * (c->cfg.copy_wg / 64);
+    const uint64_t waves = n > 8192 ? most : std::min<uint64_t>(most, std::max<uint64_t>(4 * n, (few ? 16ull : 32ull) * c->cus));
+    return launch_copy(s, (int)((waves + wpb - 1) / wpb), (int)block, b, epoch, tail);
 }
 
 // The spill pass of epoch e (overlap on, e >= 1): the groups of the epoch
@@ -1087,7 +1099,7 @@ static int enqueue_batch(devirt_ctx *c, Workspace *w, const BatchArgs &a, hipStr
         if (b.large_pages) HIPCHK(launch_translate_large(s, (int)(2ull * c->cus), 256, v, b, 0, 0));
         if ((rc = prof_end(c, s, pe))) return rc;
         if ((rc = prof_begin(c, s, 0, &pe))) return rc;
-        HIPCHK(launch_copy(s, copy_grid(c, a.n), (int)c->cfg.copy_wg, b, 0, tail));
+        HIPCHK(launch_epoch_copy(c, s, b, a.n, 0, tail));
         if ((rc = prof_end(c, s, pe))) return rc;
         w->ctr_turn ^= 1;
         w->ctr_clear = true;
@@ -1145,7 +1157,7 @@ static int enqueue_batch(devirt_ctx *c, Workspace *w, const BatchArgs &a, hipStr
                 HIPCHK(hipStreamWaitEvent(s, t_done, 0));
             }
             if ((rc = prof_begin(c, s, 0, &pe))) return rc;
-            HIPCHK(launch_copy(s, copy_grid(c, r1 - r0), (int)c->cfg.copy_wg, be, (uint32_t)e));
+            HIPCHK(launch_epoch_copy(c, s, be, r1 - r0, (uint32_t)e));
             if ((rc = prof_end(c, s, pe))) return rc;
         }
         // the spill pass uses no queue: translate(e+2) need not wait for it

@@ -85,3 +85,39 @@ def test_plain_copy_faults(name):
         assert np.array_equal(dw.pool.cpu().numpy(), o.pool)
     finally:
         ctx.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("copy_wg", [64, 256, 1024])
+def test_plain_copy_launch_shapes(copy_wg):
+    """Around the longest copy that is launched in small workgroups (32 pages per CU), both ways."""
+    import torch
+    import paper_1304_3771_amd as dv
+    sp = gen.spec("C1", mem_bytes=128 << 20, mix=(0.5, 0.5, 0.0), vmas_per_proc=1, p_np=0.0, n_requests=0, seed=4190)
+    w = gen.make_workload(sp, requests=False)
+    edge = 32 * torch.cuda.get_device_properties(0).multi_processor_count
+    base, size = (int(x) for x in w.procs[0].vmas[0])
+    rows, host = [], 0
+    for pages in (41, edge, edge + 1):
+        for d in (0, 1):
+            assert pages * 4096 <= size
+            rows.append((base + 17, host, pages * 4096 - 40, 0, d, (0, 0, 0), 0))
+            host += pages * 4096
+    w.requests = np.array(rows, gen.REQ_DTYPE)
+    w.epoch_end = np.array([len(rows)], np.uint64)
+    w.pool_bytes = host
+    o = Oracle.from_workload(w)
+    er, _ = o.batch(w.requests)
+    ctx = new_ctx(copy_wg=copy_wg)
+    try:
+        dw = device.load(ctx, w)
+        res = torch.zeros(len(rows) * 24, dtype=torch.uint8, device="cuda")
+        for i, r in enumerate(dw.reqs_host):
+            f = ctx.copy_to_guest if r["dir"] else ctx.copy_from_guest
+            f(0, int(r["gva"]), int(r["host"]), int(r["len"]), res.data_ptr() + 24 * i)
+        ctx.sync()
+        assert np.array_equal(res.cpu().numpy().view(dv.RESULT_DTYPE), er)
+        assert np.array_equal(device.read_arenas(ctx, dw)[0], o.arenas[0])
+        assert np.array_equal(dw.pool.cpu().numpy(), o.pool)
+    finally:
+        ctx.close()
