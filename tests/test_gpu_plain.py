@@ -121,3 +121,11 @@ def test_plain_copy_launch_shapes(copy_wg):
         assert np.array_equal(dw.pool.cpu().numpy(), o.pool)
     finally:
         ctx.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", ["ept", "ept_pae", "ept_lvl5", "ept_1g"])
+def test_plain_copy_ept(name):
+    """Behind an EPT, where a walk remembers its last level-2 table: tables and pages in one GiB and in two,
+    1 GiB leaves, every depth."""
+    test_plain_copy_faults(name)
