@@ -693,23 +693,24 @@ static int stage_pool(Workspace *w, uint64_t words, hipStream_t s) {
         const uint64_t cap = std::max<uint64_t>(std::max(2 * words, 2 * w->map_pool_host_cap), 1ull << 16);
         uint64_t *p = nullptr;
         HIPCHK(hipHostMalloc((void **)&p, cap * sizeof(uint64_t), hipHostMallocMapped));
+        memset(p, 0, cap * sizeof(uint64_t));  // its pages are touched here, not by the calls (25 us a pool of 4,096)
         if (w->map_pool_host) w->map_pool_old.push_back(w->map_pool_host);
         w->map_pool_host = p;
         w->map_pool_host_cap = cap;
         w->map_pool_pos = 0;
         w->map_pool_half = 0;
+        // fresh events: nothing is waited for until the new halves are left
         for (hipEvent_t &e : w->map_ev) {
             if (e) hipEventDestroy(e);
             e = nullptr;
+            HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
         }
         return 0;
     }
-    hipEvent_t &left = w->map_ev[w->map_pool_half];
-    if (!left) HIPCHK(hipEventCreateWithFlags(&left, hipEventDisableTiming));
-    HIPCHK(hipEventRecord(left, s));
+    HIPCHK(hipEventRecord(w->map_ev[w->map_pool_half], s));
     w->map_pool_half ^= 1;
     w->map_pool_pos = 0;
-    if (w->map_ev[w->map_pool_half]) HIPCHK(hipEventSynchronize(w->map_ev[w->map_pool_half]));
+    HIPCHK(hipEventSynchronize(w->map_ev[w->map_pool_half]));  // at once if never recorded
     return 0;
 }
 

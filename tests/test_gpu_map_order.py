@@ -14,6 +14,14 @@ from workload import device, gen
 
 pytestmark = pytest.mark.gpu
 
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
 TOP = {3: 3 << 30, 4: 1 << 46, 5: 1 << 55}
 
 
