@@ -3085,6 +3085,8 @@ __global__ void __launch_bounds__(256) k_map_rank_zero(const MapArgs a) {
 // found by a binary search of that run.  Only the list's first
 // min(sc[0], m) entries are keys, all distinct, so there are no ties; the
 // rest is never read.  The steps alternate between tkeys and tkeys_sorted.
+// The first one, which few workgroups have tiles for, notes the pages too
+// (with the zeroing, which fills the chip, the notes cost their full 34 us).
 constexpr uint32_t kSortTile = 1024;
 
 __device__ __forceinline__ uint64_t sort_count(const MapArgs &a) { return a.sc[0] < a.m ? a.sc[0] : a.m; }
@@ -3094,7 +3096,10 @@ __global__ void __launch_bounds__(256) k_map_tile_sort(const MapArgs a, const ui
     __shared__ uint64_t tile[kSortTile];
     const uint64_t cnt = sort_count(a);
     const uint64_t base = (uint64_t)blockIdx.x * kSortTile;
-    if (base >= cnt) return;  // uniform per block
+    if (base >= cnt) {  // uniform per block
+        note_pages(a);
+        return;
+    }
     const uint32_t len = (uint32_t)std::min<uint64_t>(kSortTile, cnt - base);
     for (uint32_t i = threadIdx.x; i < len; i += blockDim.x) tile[i] = src[base + i];
     __syncthreads();  // src may be dst: every read of the tile is done
@@ -3117,6 +3122,7 @@ __global__ void __launch_bounds__(256) k_map_tile_sort(const MapArgs a, const ui
 #pragma unroll
     for (uint32_t j = 0; j < K; ++j)
         if (threadIdx.x + 256 * j < len) dst[base + rank[j]] = key[j];
+    note_pages(a);
 }
 
 // One merge round: runs of w keys (a power of two, at least kSortTile) are
@@ -3145,7 +3151,6 @@ __global__ void __launch_bounds__(256) k_map_merge(const MapArgs a, const uint64
 
 // Zero the new tables (after a long list's sort).
 __global__ void __launch_bounds__(256) k_map_zero(const MapArgs a) {
-    note_pages(a);
     const uint64_t nt = new_tables(a);
     DVm zvm;
     if (!nt || !map_vm(a, zvm)) return;
@@ -3256,8 +3261,10 @@ hipError_t launch_map(hipStream_t s, const MapArgs &a) {
         for (uint64_t w = kSortTile; w < a.m; w *= 2) ++rounds;
         uint64_t *buf[2] = {a.tkeys, a.tkeys_sorted};
         uint32_t cur = (rounds & 1) ? 0 : 1;
-        hipLaunchKernelGGL(k_map_tile_sort, dim3((unsigned)((a.m + kSortTile - 1) / kSortTile)), dim3(256), 0, s, a,
-                           a.tkeys, buf[cur]);
+        const uint64_t notes = std::min<uint64_t>(a.n, 1ull << 18);  // lanes
+        const uint64_t tiles = (a.m + kSortTile - 1) / kSortTile;
+        hipLaunchKernelGGL(k_map_tile_sort, dim3((unsigned)std::max<uint64_t>(tiles, blocks_for(notes))), dim3(256), 0,
+                           s, a, a.tkeys, buf[cur]);
         const unsigned mblocks = blocks_for(std::min<uint64_t>(a.m, 1ull << 22));
         for (uint64_t w = kSortTile; w < a.m; w *= 2) {
             hipLaunchKernelGGL(k_map_merge, dim3(mblocks), dim3(256), 0, s, a, buf[cur], buf[cur ^ 1], w);

@@ -685,12 +685,14 @@ int dv_map_pool_check(const devirt_ctx *c, uint32_t asid, const uint64_t *pool_g
 // one is used once the calls staged there have passed theirs.  A larger buffer
 // replaces one that is too small, also while the caller captures the stream
 // (no event can be waited for then); the old one is kept until the end, at
-// most as much again as the current one, since the size doubles.
+// most as much again as the current one, since the size at least doubles.
 static int stage_pool(Workspace *w, uint64_t words, hipStream_t s) {
     const bool fits = 2 * words <= w->map_pool_host_cap;
     if (fits && w->map_pool_pos + words <= w->map_pool_host_cap / 2) return 0;
     if (!fits || stream_capturing(s)) {
-        const uint64_t cap = std::max<uint64_t>(std::max(2 * words, 2 * w->map_pool_host_cap), 1ull << 16);
+        // halves of four such calls, while that is no more than 8 MiB in all
+        const uint64_t calls = std::max<uint64_t>(2 * words, std::min<uint64_t>(8 * words, 1ull << 20));
+        const uint64_t cap = std::max<uint64_t>(std::max(calls, 2 * w->map_pool_host_cap), 1ull << 16);
         uint64_t *p = nullptr;
         HIPCHK(hipHostMalloc((void **)&p, cap * sizeof(uint64_t), hipHostMallocMapped));
         memset(p, 0, cap * sizeof(uint64_t));  // its pages are touched here, not by the calls (25 us a pool of 4,096)
